@@ -14,8 +14,8 @@ namespace {
 // the input g (g[t - Hx]). VIRT = false: no history, t indexes g directly.
 template <bool VIRT>
 struct RowRef {
-  const float* g;
-  const float* h;
+  gbl_f32* g;
+  gbl_f32* h;
   int Hx;
   __device__ __forceinline__ float at(int t) const {
     if (VIRT) return *(t < Hx ? h + t : g + (t - Hx));  // one load from the selected address
@@ -53,9 +53,9 @@ struct Chain {
 // Element of 0-based rank `rank` of the keys of samples [lo, hi):
 // MODE 0 keys are x ^ 0x80000000 (order of int32 x), MODE 1 keys are |x - m|.
 // Four passes over the window, 8 key bits each; H[0..255] serves as the
-// digit histogram (callers rebuild or abandon the value histogram afterwards).
+// digit histogram (callers recount or abandon the value histogram afterwards).
 template <int MODE, bool VIRT>
-__device__ uint32_t radix_select(uint32_t* H, const RowRef<VIRT>& row, int lo, int hi, int rank, int m, int lane) {
+__device__ __forceinline__ uint32_t radix_select(uint32_t* H, const RowRef<VIRT>& row, int lo, int hi, int rank, int m, int lane) {
   uint32_t prefix = 0, pmask = 0;
   for (int shift = 24; shift >= 0; shift -= 8) {
     for (int i = lane; i < 256; i += 64) H[i] = 0;
@@ -92,112 +92,150 @@ __device__ uint32_t radix_select(uint32_t* H, const RowRef<VIRT>& row, int lo, i
   return prefix;
 }
 
-// Recount the window [lo, hi) into a histogram whose bin 0 is `base`;
-// returns #{x < base}.
+// Recount the window [lo, hi) into a histogram centred on `centre`, and the
+// pivots' counts for median m0 and MAD d0 (guesses or known values) from the
+// samples themselves. Bound by load latency: the next eight wave loads are in
+// flight while eight are counted (one load at a time, a 4096-sample recount took 64 dependent
+// round trips to L2).
 template <int NB, bool VIRT>
-__device__ int rebuild(Chain<NB, VIRT>& c, int lo, int hi, int base) {
-  c.base = base;
-  for (int i = c.lane; i < NB / 2; i += 64) c.H[i] = 0;
+__device__ __forceinline__ void recount(Chain<NB, VIRT>& c, int lo, int hi, int centre, int m0, int d0) {
+  constexpr int kU = 8;
+  c.base = centre - NB / 2;
+  c.m = m0;
+  c.d = d0;
+  for (int i = 4 * c.lane; i < NB / 2; i += 256) *reinterpret_cast<uint4*>(&c.H[i]) = make_uint4(0u, 0u, 0u, 0u);
   wave_lds_fence();
-  int below = 0;
-  for (int t0 = lo; t0 < hi; t0 += 64) {
-    const int t = t0 + c.lane;
-    const bool ok = t < hi;
-    const int v = ok ? c.row.iat(t) : 0;
-    const uint32_t idx = (uint32_t)v - (uint32_t)base;
-    if (ok && idx < (uint32_t)NB) hist_add(c.H, idx, 1u);
-    below += popc(ballot(ok && v < base));
+  const int pL = m0 - d0, pU = m0 + d0 + 1;
+  int cm = 0, cL = 0, cU = 0;
+  float nv[kU];
+  auto fetch = [&](int t0) {
+#pragma unroll
+    for (int q = 0; q < kU; ++q) nv[q] = c.row.at(min(t0 + 64 * q + c.lane, hi - 1));
+  };
+  fetch(lo);
+  for (int t0 = lo; t0 < hi; t0 += 64 * kU) {
+    float v[kU];
+#pragma unroll
+    for (int q = 0; q < kU; ++q) v[q] = nv[q];
+    fetch(t0 + 64 * kU);
+#pragma unroll
+    for (int q = 0; q < kU; ++q) {
+      const bool ok = t0 + 64 * q + c.lane < hi;
+      const uint64_t okm = ballot(ok);
+      const int x = (int)v[q];
+      const uint32_t idx = (uint32_t)x - (uint32_t)c.base;
+      if (ok && idx < (uint32_t)NB) hist_add(c.H, idx, 1u);
+      cm += popc(ballot(x < m0) & okm);
+      cL += popc(ballot(x < pL) & okm);
+      cU += popc(ballot(x < pU) & okm);
+    }
   }
   wave_lds_fence();
+  c.cm = cm;
+  c.cL = cL;
+  c.cU = cU;
   c.raw = false;
-  return below;
 }
 
-// Median and MAD from the whole histogram, given #{x < base}. Fails (returns
-// false) when a needed quantile lies outside the histogram's range.
-template <int NB, bool VIRT>
-__device__ bool full_query(Chain<NB, VIRT>& c, int below) {
-  const int rho = (c.n - 1) >> 1;
-  if (below > rho) return false;
-  int acc = below, m2 = 0, cm2 = 0;
-  bool found = false;
-  for (int i0 = 0; i0 < NB; i0 += 64) {
-    const int h = hist_get(c.H, i0 + c.lane);
-    const int inc = wave_scan_incl(h);
-    const uint64_t mk = ballot(acc + inc > rho);
-    if (mk) {
-      const int j = ctz(mk);
-      m2 = c.base + i0 + j;
-      cm2 = acc + readlane(inc, j) - readlane(h, j);
-      found = true;
-      break;
-    }
-    acc += readlane(inc, 63);
-  }
-  if (!found) return false;
-  // MAD: fold the histogram at m2; g(0) = h(m2), g(e) = h(m2 + e) + h(m2 - e).
-  const int i2 = m2 - c.base;
-  int acc_lo = 0, acc_hi = 0;
-  for (int e0 = 0;; e0 += 64) {
-    const int e = e0 + c.lane;
-    const bool in_hi = i2 + e < NB, in_lo = i2 - e >= 0;
-    const int ghi = in_hi ? hist_get(c.H, i2 + e) : 0;
-    const int glo = (e > 0 && in_lo) ? hist_get(c.H, i2 - e) : 0;
-    const int ihi = wave_scan_incl(ghi), ilo = wave_scan_incl(glo);
-    const bool ok = in_hi && in_lo;
-    const uint64_t okm = ballot(ok);
-    const uint64_t mk = ballot(ok && acc_lo + acc_hi + ihi + ilo > rho);
-    if (mk) {  // okm is a prefix of the lanes, so every e <= j was in range
-      const int j = ctz(mk);
-      c.m = m2;
-      c.cm = cm2;
-      c.d = e0 + j;
-      c.cL = cm2 - (acc_lo + readlane(ilo, j));
-      c.cU = cm2 + acc_hi + readlane(ihi, j);
-      return true;
-    }
-    if (okm != ~0ull) return false;
-    acc_lo += readlane(ilo, 63);
-    acc_hi += readlane(ihi, 63);
-  }
+template <int NB>
+__device__ __forceinline__ int hist_or_0(const uint32_t* H, int i) {
+  const int k = min(max(i, 0), NB - 1);
+  const int h = hist_get(H, k);
+  return i == k ? h : 0;
 }
 
-// Local query: new median within 31 values of the old one and new MAD within
-// 31 of the old one (the usual case). Returns false when it cannot decide.
+// General query: walks from the current pivots, 64 bins a step, to the new
+// median and from there to the new MAD; any distance inside the histogram.
+// The cost is a few steps per 64 values moved, so a baseline that moves by a
+// large part of a sigma per block (a drift shorter than the window) stays
+// within a small factor of the narrow query. Returns false, with the chain
+// unchanged, when a pivot leaves the histogram.
 template <int NB, bool VIRT>
-__device__ __forceinline__ bool fast_query(Chain<NB, VIRT>& c) {
-  const int rho = (c.n - 1) >> 1;
-  const int im = c.m - c.base, iL = c.m - c.d - c.base, iU = c.m + c.d + 1 - c.base;
-  if (im - 32 < 0 || im + 32 > NB || iL - 32 < 0 || iU + 32 > NB) return false;
-  const int lane = c.lane;
-  const int h = hist_get(c.H, im - 32 + lane);
-  const int hL = hist_get(c.H, iL - 32 + lane);
-  const int hU = hist_get(c.H, iU - 32 + lane);
-  const int inc = wave_scan_incl(h), incL = wave_scan_incl(hL), incU = wave_scan_incl(hU);
-  const int lt = c.cm - readlane(inc, 31) + inc - h;  // #{x < m - 32 + lane}
-  const uint64_t mk = ballot(lt + h > rho);
-  if (!mk) return false;
+__device__ __forceinline__ bool walk_query(Chain<NB, VIRT>& c) {
+  const int rho = (c.n - 1) >> 1, lane = c.lane;
+  const int im = c.m - c.base;
+  int iL = im - c.d, iU = im + c.d + 1;
+  if (c.d < 0 || iL < 0 || iU > NB) return false;
+  // median: windows of 64 bins from p, cp = #{x < base + p}
+  int p = im - 32;
+  int h = hist_or_0<NB>(c.H, p + lane), inc = wave_scan_incl(h);
+  int cp = c.cm - readlane(inc, 31);
+  uint64_t mk;
+  while (true) {
+    if (cp > rho) {
+      if (p <= 0) return false;
+      p -= 64;
+      h = hist_or_0<NB>(c.H, p + lane);
+      inc = wave_scan_incl(h);
+      cp -= readlane(inc, 63);
+    } else {
+      mk = ballot(cp + inc > rho);
+      if (mk) break;
+      if (p + 64 >= NB) return false;
+      p += 64;
+      cp += readlane(inc, 63);
+      h = hist_or_0<NB>(c.H, p + lane);
+      inc = wave_scan_incl(h);
+    }
+  }
   const int j = ctz(mk);
-  const int ltj = readlane(lt, j);
-  if (ltj > rho) return false;  // median below the window
-  const int delta = j - 32;      // new median - old median
-  const int ltL = c.cL - readlane(incL, 31) + incL - hL;  // #{x < (m - d) - 32 + lane}
-  const int ltU = c.cU - readlane(incU, 31) + incU - hU;  // #{x < (m + d + 1) - 32 + lane}
-  // lane tests d' = d + lane - 32 around the new median m + delta:
-  // #{|x - m'| <= d'} = #{x < m' + d' + 1} - #{x < m' - d'}
-  const int a = delta + 64 - lane, b = delta + lane;
-  const int dp = c.d + lane - 32;
-  const bool ok = a >= 0 && a < 64 && b >= 0 && b < 64 && dp >= 0;
-  const int va = __shfl(ltL, a & 63, 64), vb = __shfl(ltU, b & 63, 64);
-  const uint64_t okm = ballot(ok), fm = ballot(ok && vb - va > rho);
-  if (!fm) return false;
-  const int jj = ctz(fm);
-  if (jj == ctz(okm) && readlane(dp, jj) > 0) return false;  // MAD may be smaller still
-  c.m = c.m + delta;
-  c.cm = ltj;
-  c.d = readlane(dp, jj);
-  c.cL = readlane(va, jj);
-  c.cU = readlane(vb, jj);
+  const int im2 = p + j, cm2 = cp + readlane(inc, j) - readlane(h, j);
+  // the outer pivots follow the median at the old MAD
+  const int delta = im2 - im;
+  int cL = c.cL, cU = c.cU;
+  {
+    const int len = delta < 0 ? -delta : delta;
+    const int aL = delta < 0 ? iL + delta : iL, aU = delta < 0 ? iU + delta : iU;
+    if (aL < 0 || iL + delta < 0 || iU + delta > NB) return false;
+    int sL = 0, sU = 0;
+    for (int i = lane; i < len; i += 64) {
+      sL += hist_get(c.H, aL + i);
+      sU += hist_get(c.H, aU + i);
+    }
+    sL = wave_sum_u(sL);
+    sU = wave_sum_u(sU);
+    cL += delta < 0 ? -sL : sL;
+    cU += delta < 0 ? -sU : sU;
+    iL += delta;
+    iU += delta;
+  }
+  // MAD: #{|x - m| <= d} = cU - cL; one bin at each side per unit of d
+  int d = c.d;
+  if (cU - cL > rho) {  // at most d: lane l tests d - 1 - l
+    while (true) {
+      const bool ok = lane < d;
+      const int hU = ok ? hist_get(c.H, iU - 1 - lane) : 0, hL = ok ? hist_get(c.H, iL + lane) : 0;
+      const int incU = wave_scan_incl(hU), incL = wave_scan_incl(hL);
+      const int k = popc(ballot(ok && cU - cL - incU - incL > rho));  // the first k lanes
+      if (k == 0) break;
+      cU -= readlane(incU, k - 1);
+      cL += readlane(incL, k - 1);
+      d -= k;
+      iU -= k;
+      iL += k;
+      if (k < 64) break;
+    }
+  } else {  // more than d: lane l tests d + 1 + l
+    while (true) {
+      const bool ok = iU + lane < NB && iL - 1 - lane >= 0;
+      const int hU = ok ? hist_get(c.H, iU + lane) : 0, hL = ok ? hist_get(c.H, iL - 1 - lane) : 0;
+      const int incU = wave_scan_incl(hU), incL = wave_scan_incl(hL);
+      const uint64_t mm = ballot(ok && cU - cL + incU + incL > rho);
+      const int k = mm ? ctz(mm) : 63;
+      if (!mm && ballot(!ok)) return false;
+      cU += readlane(incU, k);
+      cL -= readlane(incL, k);
+      d += k + 1;
+      iU += k + 1;
+      iL -= k + 1;
+      if (mm) break;
+    }
+  }
+  c.m = c.base + im2;
+  c.cm = cm2;
+  c.d = d;
+  c.cL = cL;
+  c.cU = cU;
   return true;
 }
 
@@ -249,36 +287,9 @@ __device__ __forceinline__ bool narrow_query(Chain<NB, VIRT>& c) {
   return true;
 }
 
-// Exact answer for window [lo, hi) from the samples themselves, then a
-// histogram centred on the median when the data allow one.
-template <int NB, bool VIRT>
-__device__ void exact_block(Chain<NB, VIRT>& c, int lo, int hi) {
-  const int rho = (c.n - 1) >> 1;
-  const int m = (int)(radix_select<0, VIRT>(c.H, c.row, lo, hi, rho, 0, c.lane) ^ 0x80000000u);
-  const uint32_t d = radix_select<1, VIRT>(c.H, c.row, lo, hi, rho, m, c.lane);
-  c.m = m;
-  c.d = (int)d;
-  if (d < (uint32_t)(NB / 2 - 128)) {
-    const int below = rebuild(c, lo, hi, m - NB / 2);
-    const bool ok = full_query(c, below);  // succeeds: both quantiles are in range
-    c.raw = !ok;
-  } else {
-    c.raw = true;
-  }
-}
-
-// Median of up to 256 samples spread evenly over [lo, hi) (four per lane):
-// a bitwise binary search on the order-preserving keys, counted with ballots.
-template <bool VIRT>
-__device__ int sample_median(const RowRef<VIRT>& row, int lo, int hi, int lane) {
-  const int n = hi - lo;
-  const int ns = n < 256 ? n : 256;
-  uint32_t k[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int i = lane + 64 * q;
-    k[q] = i < ns ? ((uint32_t)row.iat(lo + (int)(((int64_t)i * n) / ns)) ^ 0x80000000u) : 0xFFFFFFFFu;
-  }
+// Lower median of the wave's 4 x 64 keys, the first ns of them in use (the
+// others ~0): a bitwise binary search counted with ballots.
+__device__ __forceinline__ uint32_t key_median(const uint32_t (&k)[4], int ns) {
   const int rank = (ns - 1) >> 1;
   uint32_t p = 0;  // largest key with #{k < p} <= rank
   for (int b = 31; b >= 0; --b) {
@@ -288,69 +299,148 @@ __device__ int sample_median(const RowRef<VIRT>& row, int lo, int hi, int lane) 
     for (int q = 0; q < 4; ++q) cnt += popc(ballot(k[q] < cand));
     if (cnt <= rank) p = cand;
   }
-  return (int)(p ^ 0x80000000u);
+  return p;
 }
 
-// span_hi >= hi: the samples that centre the histogram are spread over
-// [lo, span_hi) (the windows this chain will see, when the first is clipped).
-template <int NB, bool VIRT>
-__device__ void chain_init(Chain<NB, VIRT>& c, int lo, int hi, int span_hi) {
-  // Centre the first histogram on the median of samples spread over the
-  // whole window (a contiguous run of samples can sit far from it when the
-  // data drift); for a window clipped at the row start, over the samples the
-  // growing windows will take in, so that it need not be recentred (and the
-  // window recounted) as they grow.
-  const int g = sample_median(c.row, lo, span_hi, c.lane);
-  const int below = rebuild(c, lo, hi, g - NB / 2);
-  if (!full_query(c, below)) exact_block(c, lo, hi);
-}
-
-// Rare path: answer from the whole histogram, recentre it when the quantiles
-// near its edges, or fall back to the exact select. Kept out of line so the
-// unrolled block loop stays small.
-template <int NB, bool VIRT>
-__device__ void slow_block(Chain<NB, VIRT>& c, int lo, int hi) {
-  // #{x < base} from the exact count below the old median
-  const int im = c.m - c.base;
-  int s = 0;
-  for (int i0 = 0; i0 < im; i0 += 64) {
-    const int i = i0 + c.lane;
-    s += i < im ? hist_get(c.H, i) : 0;
+// Median and MAD of up to 256 samples spread evenly over [lo, hi) (four per lane).
+template <bool VIRT>
+__device__ __forceinline__ void sample_stats(const RowRef<VIRT>& row, int lo, int hi, int lane, int& m, int& d) {
+  const int n = hi - lo;
+  const int ns = n < 256 ? n : 256;
+  int x[4];
+  uint32_t k[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int i = min(lane + 64 * q, ns - 1);
+    x[q] = row.iat(lo + (int)(((int64_t)i * n) / ns));
   }
-  const int below = c.cm - wave_sum_u(s);
-  if (full_query(c, below)) {
-    // keep the local queries' windows inside the histogram: recentre near an edge
-    if (c.m - c.d - 96 < c.base || c.m + c.d + 97 > c.base + NB) {
-      if (c.d < NB / 2 - 128) {
-        const int b2 = rebuild(c, lo, hi, c.m - NB / 2);
-        c.raw = !full_query(c, b2);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) k[q] = lane + 64 * q < ns ? ((uint32_t)x[q] ^ 0x80000000u) : 0xFFFFFFFFu;
+  m = (int)(key_median(k, ns) ^ 0x80000000u);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) k[q] = lane + 64 * q < ns ? absdiff(x[q], m) : 0xFFFFFFFFu;
+  d = (int)key_median(k, ns);
+}
+
+// The answer of window [lo, hi) where the narrow query did not give it. What
+// is tried, in order (one site for each, so that the code stays small):
+//   the walk, from a chain in use (kWalk);
+//   a new histogram and new pivots (kFresh, also a chain's first block; when
+//   the quantiles moved out of the histogram), then the walk. The histogram
+//   is centred on the median of samples spread over [lo, span_hi): a
+//   contiguous run of samples can sit far from the window's median when the
+//   data drift, and for a window clipped at the row start (span_hi > hi) the
+//   samples that the growing windows will take in count too, so that it need
+//   not be recentred as they grow. The pivots start from the sample median
+//   and MAD of the window itself;
+//   the exact select (kExact, also every block while the data are too spread
+//   for the histogram), then a histogram about its result where one fits.
+// A walk that ends near the histogram's edge recentres it (kCentre), to keep
+// the local queries' windows inside.
+enum { kWalk = 0, kFresh = 1, kExact = 2, kCentre = 3 };
+
+template <int NB, bool VIRT>
+__device__ __forceinline__ void refresh_body(Chain<NB, VIRT>& c, int mode, int lo, int hi, int span_hi) {
+  while (true) {
+    if (mode != kWalk) {
+      int centre = c.m, m0 = c.m, d0 = c.d;
+      if (mode == kFresh) {
+        sample_stats(c.row, lo, span_hi, c.lane, centre, d0);
+        m0 = centre;
+        if (span_hi != hi) sample_stats(c.row, lo, hi, c.lane, m0, d0);
+      } else if (mode == kExact) {
+        const int rho = (c.n - 1) >> 1;
+        m0 = (int)(radix_select<0, VIRT>(c.H, c.row, lo, hi, rho, 0, c.lane) ^ 0x80000000u);
+        d0 = (int)radix_select<1, VIRT>(c.H, c.row, lo, hi, rho, m0, c.lane);
+        centre = m0;
+        if ((uint32_t)d0 >= (uint32_t)(NB / 2 - 128)) {
+          c.m = m0;
+          c.d = d0;
+          c.raw = true;
+          return;
+        }
       }
+      recount(c, lo, hi, centre, m0, d0);
+      if (mode != kFresh) return;
     }
-    return;
+    if (!walk_query(c)) {
+      mode = mode == kWalk ? kFresh : kExact;
+      continue;
+    }
+    if (mode == kFresh || c.d >= NB / 2 - 128 || (c.m - c.d - 96 >= c.base && c.m + c.d + 97 <= c.base + NB)) return;
+    mode = kCentre;
   }
-  exact_block(c, lo, hi);
+}
+
+// refresh_body as one real call for all its sites, the chain's state passed
+// and returned by value in registers: inlined at five sites it spilled the
+// block loop's scalar registers, and by reference the state lives in memory.
+// (Pointers go with their address space: through generic ones the call would
+// use flat accesses.)
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+
+struct ChainState {
+  int base, m, cm, d, cL, cU, raw;
+};
+
+template <int NB, bool VIRT>
+__device__ __noinline__ ChainState refresh_call(lds_u32* H, gbl_f32* g, gbl_f32* h, int Hx, int n, int base,
+                                                int m, int cm, int d, int cL, int cU, int mode, int lo, int hi,
+                                                int span_hi) {
+  Chain<NB, VIRT> c;
+  c.H = (uint32_t*)H;
+  c.row.g = uniform_ptr(g);
+  c.row.h = VIRT ? uniform_ptr(h) : g;
+  c.row.Hx = VIRT ? readfirst(Hx) : 0;
+  c.lane = lane_id();
+  c.n = readfirst(n);
+  c.base = readfirst(base);
+  c.m = readfirst(m);
+  c.cm = readfirst(cm);
+  c.d = readfirst(d);
+  c.cL = readfirst(cL);
+  c.cU = readfirst(cU);
+  c.raw = false;
+  refresh_body(c, readfirst(mode), readfirst(lo), readfirst(hi), readfirst(span_hi));
+  return {c.base, c.m, c.cm, c.d, c.cL, c.cU, c.raw ? 1 : 0};
 }
 
 template <int NB, bool VIRT>
+__device__ __forceinline__ void refresh(Chain<NB, VIRT>& c, int mode, int lo, int hi, int span_hi) {
+  const ChainState s = refresh_call<NB, VIRT>((lds_u32*)c.H, c.row.g, c.row.h, c.row.Hx, c.n, c.base, c.m, c.cm, c.d, c.cL, c.cU,
+                                              mode, lo, hi, span_hi);
+  c.base = readfirst(s.base);
+  c.m = readfirst(s.m);
+  c.cm = readfirst(s.cm);
+  c.d = readfirst(s.d);
+  c.cL = readfirst(s.cL);
+  c.cU = readfirst(s.cU);
+  c.raw = readfirst(s.raw) != 0;
+}
+
+// Moves the window to the next block: av enters and bv leaves in the lanes of
+// a_ok and b_ok (FULL: in every lane, the window's size unchanged).
+template <bool FULL, int NB, bool VIRT>
 __device__ __forceinline__ void chain_step(Chain<NB, VIRT>& c, int lo, int hi, bool a_ok, int av, bool b_ok, int bv) {
   // lane masks of the entering (a) and leaving (b) samples; the counts below
   // AND raw comparison ballots with them (a comparison's ballot is its own
   // lane mask, a combined condition would be materialised and compared again)
-  const uint64_t aM = ballot(a_ok), bM = ballot(b_ok);
-  c.n += popc(aM) - popc(bM);
-  if (c.raw) {
-    exact_block(c, lo, hi);
-    return;
+  const uint64_t aM = FULL ? ~0ull : ballot(a_ok), bM = FULL ? ~0ull : ballot(b_ok);
+  if (!FULL) c.n += popc(aM) - popc(bM);
+  int mode = kExact;
+  if (!c.raw) {
+    const uint32_t ua = (uint32_t)av - (uint32_t)c.base, ub = (uint32_t)bv - (uint32_t)c.base;
+    if ((FULL || a_ok) && ua < (uint32_t)NB) hist_add(c.H, ua, 1u);
+    if ((FULL || b_ok) && ub < (uint32_t)NB) hist_add(c.H, ub, 0xFFFFFFFFu);
+    const int pL = c.m - c.d, pU = c.m + c.d + 1;
+    c.cm += popc(ballot(av < c.m) & aM) - popc(ballot(bv < c.m) & bM);
+    c.cL += popc(ballot(av < pL) & aM) - popc(ballot(bv < pL) & bM);
+    c.cU += popc(ballot(av < pU) & aM) - popc(ballot(bv < pU) & bM);
+    wave_lds_fence();
+    if (narrow_query(c)) return;
+    mode = kWalk;
   }
-  const uint32_t ua = (uint32_t)av - (uint32_t)c.base, ub = (uint32_t)bv - (uint32_t)c.base;
-  if (a_ok && ua < (uint32_t)NB) hist_add(c.H, ua, 1u);
-  if (b_ok && ub < (uint32_t)NB) hist_add(c.H, ub, 0xFFFFFFFFu);
-  const int pL = c.m - c.d, pU = c.m + c.d + 1;
-  c.cm += popc(ballot(av < c.m) & aM) - popc(ballot(bv < c.m) & bM);
-  c.cL += popc(ballot(av < pL) & aM) - popc(ballot(bv < pL) & bM);
-  c.cU += popc(ballot(av < pU) & aM) - popc(ballot(bv < pU) & bM);
-  wave_lds_fence();
-  if (!narrow_query(c) && !fast_query(c)) slow_block(c, lo, hi);
+  refresh(c, mode, lo, hi, hi);
 }
 
 // WPG chains (waves) per workgroup; LDS = WPG * NB * 2 bytes. Blocks
@@ -368,56 +458,75 @@ __device__ __forceinline__ void stats_chain(const StatsArgs& a, const int chain,
   const int t0 = a.tmin ? *a.tmin : 0;
   Chain<NB, VIRT> c;
   c.H = H;
-  c.row.g = a.x + (int64_t)row * a.ld;
-  c.row.h = VIRT ? a.hist + (int64_t)row * a.ldh : nullptr;
+  c.row.g = (gbl_f32*)a.x + (int64_t)row * a.ld;
+  c.row.h = VIRT ? (gbl_f32*)a.hist + (int64_t)row * a.ldh : c.row.g;
   c.row.Hx = VIRT ? a.Hx : 0;
   c.L = L;
   c.lane = lane;
-  int32_t* med = a.med + (int64_t)row * a.nblocks;
-  int32_t* mad = a.mad + (int64_t)row * a.nblocks;
+  gbl_i32* med = (gbl_i32*)a.med + (int64_t)row * a.nblocks;
+  gbl_i32* mad = (gbl_i32*)a.mad + (int64_t)row * a.nblocks;
 
   // Block k's window is [max(t0, E_k - L), min(N, E_k)) with E_k = min(64k + 64, N) + lead:
   // from block k-1 to k the samples [min(N, E_{k-1}), min(N, E_k)) enter it and
   // [max(t0, E_{k-1} - L), max(t0, E_k - L)) leave it, at most 64 each.
-  {
-    const int E = min(kb0 * kStride + kStride, N) + lead;
-    const int e = min(N, E), lo = max(t0, E - L);
-    c.n = e - lo;
-    chain_init(c, lo, e, min(N, max(e, lo + L)));
-    if (lane == 0) { med[kb0] = c.m; mad[kb0] = c.d; }
-  }
-
-  // Samples entering / leaving the window at block kk, prefetched 4 blocks
-  // ahead. Every lane loads (from a clamped in-row position) and unused lanes
-  // are zeroed afterwards: loads skipped under a branch would leave the
-  // compiler unsure how many are in flight, and it would then wait for all of
-  // them, the prefetch included, before each block.
-  auto fetch = [&](int kk, float& va, float& vb) {
-    const int Ep = min(kk * kStride, N) + lead, E = min(kk * kStride + kStride, N) + lead;
-    const int ep = min(N, Ep), e = min(N, E), lp = max(t0, Ep - L), l2 = max(t0, E - L);
-    const float ra = c.row.at(min(ep + lane, N - 1)), rb = c.row.at(min(lp + lane, N - 1));
-    va = (lane < e - ep) ? ra : 0.f;
-    vb = (lane < l2 - lp) ? rb : 0.f;
-  };
-  float pa[4], pb[4];
+  // Interior blocks [fi, fe), where exactly 64 enter and 64 leave
+  // (64 kk + lead >= t0 + L and 64 kk + 64 + lead <= N), are walked four at a
+  // time without clamps or lane masks; the others (a row's first windows, and
+  // its last) one by one.
+  const int fi = max(kb0 + 1, (t0 + L - lead + kStride - 1) / kStride);
+  const int fe = min(kb1, (N - lead) / kStride);
+  const int fend = fe - fi >= 4 ? fi + (fe - fi) / 4 * 4 : fi;
+  int kk = kb0;
+  while (true) {
+    const int stop = fend > fi && kk < fend ? fi : kb1;
+    // a lane's entering and leaving samples of block kk (a clamped in-row position where unused)
+    float na, nb;
+    auto fetch = [&](int k) {
+      const int Ep = min(k * kStride, N) + lead;
+      na = c.row.at(min(min(N, Ep) + lane, N - 1));
+      nb = c.row.at(min(max(t0, Ep - L) + lane, N - 1));
+    };
+    fetch(kk);
+    for (; kk < stop; ++kk) {
+      const int Ep = min(kk * kStride, N) + lead, E = min(kk * kStride + kStride, N) + lead;
+      const int ep = min(N, Ep), e = min(N, E), lp = max(t0, Ep - L), lo = max(t0, E - L);
+      const float va = na, vb = nb;
+      fetch(kk + 1);
+      if (kk == kb0) {
+        c.n = e - lo;
+        c.raw = false;
+        refresh(c, kFresh, lo, e, min(N, max(e, lo + L)));
+      } else {
+        chain_step<false>(c, lo, e, lane < e - ep, (int)va, lane < lo - lp, (int)vb);
+      }
+      // every lane stores the same (wave-uniform) values: no branch around the stores
+      med[kk] = c.m;
+      mad[kk] = c.d;
+    }
+    if (kk >= kb1) break;
+    // Samples are prefetched four blocks ahead, by every lane: loads under a
+    // branch would leave the compiler unsure how many are in flight, and it
+    // would then wait for all of them, the prefetch included, before each block.
+    float pa[4], pb[4];
+    auto fetch_full = [&](int k, float& va, float& vb) {
+      va = c.row.at(k * kStride + lead + lane);
+      vb = c.row.at(k * kStride + lead - L + lane);
+    };
 #pragma unroll
-  for (int j = 0; j < 4; ++j) fetch(kb0 + 1 + j, pa[j], pb[j]);
-
-  for (int k = kb0 + 1; k < kb1; k += 4) {
+    for (int j = 0; j < 4; ++j) fetch_full(kk + j, pa[j], pb[j]);
+    for (; kk < fend; kk += 4) {
+      const int kn = kk + 4 < fend ? kk + 4 : kk;  // the last group fetches itself again
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int kk = k + j;
-      const float va = pa[j], vb = pb[j];
-      fetch(kk + 4, pa[j], pb[j]);
-      if (kk < kb1) {
-        const int Ep = min(kk * kStride, N) + lead, E = min(kk * kStride + kStride, N) + lead;
-        const int ep = min(N, Ep), e = min(N, E), lp = max(t0, Ep - L), l2 = max(t0, E - L);
-        chain_step(c, l2, e, lane < e - ep, (int)va, lane < l2 - lp, (int)vb);
-        // every lane stores the same (wave-uniform) values: no branch around the stores
-        med[kk] = c.m;
-        mad[kk] = c.d;
+      for (int j = 0; j < 4; ++j) {
+        const float va = pa[j], vb = pb[j];
+        fetch_full(kn + j, pa[j], pb[j]);
+        const int e = (kk + j) * kStride + kStride + lead;
+        chain_step<true>(c, e - L, e, true, (int)va, true, (int)vb);
+        med[kk + j] = c.m;
+        mad[kk + j] = c.d;
       }
     }
+    if (kk >= kb1) break;
   }
 }
 

@@ -214,7 +214,7 @@ __device__ __forceinline__ int group_shift(int w) {
 // One array per kernel, whoever asks: the fused batch kernel keeps its
 // statistics histograms in it before the workgroup turns to detection.
 __device__ __forceinline__ uint32_t* detect_ring() {
-  __shared__ uint32_t ring[kRing];
+  __shared__ __align__(16) uint32_t ring[kRing];
   return ring;
 }
 
@@ -241,10 +241,10 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
   const int s0 = A.seg_base + seg * A.seg_len;
   const int s1 = min(N, s0 + A.seg_len);
   // virtual sample t: t < Hx from the history row, else x row at t - Hx
-  const float* xr = A.x + (int64_t)row * A.ld - (VIRT ? A.Hx : 0);
-  const float* hr = VIRT ? A.hist + (int64_t)row * A.ldh : nullptr;
-  const int32_t* medr = A.med + (int64_t)row * A.nblocks;
-  const int32_t* madr = A.mad + (int64_t)row * A.nblocks;
+  gbl_f32* xr = (gbl_f32*)A.x + (int64_t)row * A.ld - (VIRT ? A.Hx : 0);
+  gbl_f32* hr = VIRT ? (gbl_f32*)A.hist + (int64_t)row * A.ldh : xr;
+  const gbl_i32* medr = (const gbl_i32*)A.med + (int64_t)row * A.nblocks;
+  const gbl_i32* madr = (const gbl_i32*)A.mad + (int64_t)row * A.nblocks;
   const int emax = min(s1 - s0 + A.maxw - 1, N - s0);  // last window end needed
   const int nsteps = (emax + 64) / kC + 1;              // + group shift headroom
   const bool vec = ((reinterpret_cast<uintptr_t>(A.x + (int64_t)row * A.ld) & 15u) == 0) &&
@@ -262,7 +262,7 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
   const double tsq = tthr ? A.sqrtw[tj] : 1.0;
   const int tw = 1 << tj;
   const int tk0 = s0 - group_shift(tw) - (tw - (tw >> 1));  // centre of group 0, step 0
-  const int32_t* wmadr = A.wmad ? A.wmad + (int64_t)row * A.nw : nullptr;
+  const gbl_i32* wmadr = A.wmad ? (const gbl_i32*)A.wmad + (int64_t)row * A.nw : nullptr;
   auto fetch_mad = [&](int c) -> int {
     if (!tthr) return 0;
     // one scale per (row, width): positions outside the row are masked out
@@ -277,9 +277,9 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
     if (t0 < N) {
       mk = medr[t0 >> 6];
       // a step never straddles the history end (both are multiples of 1024)
-      const float* src = (VIRT && s0 + c * kC < A.Hx) ? hr : xr;
+      gbl_f32* src = (VIRT && s0 + c * kC < A.Hx) ? hr : xr;
       if (vec && t0 + 3 < N) {
-        const float4 v = *reinterpret_cast<const float4*>(src + t0);
+        const f32x4 v = *(gbl_f32x4*)(src + t0);
         f0 = v.x; f1 = v.y; f2 = v.z; f3 = v.w;
       } else {
         f0 = src[t0];

@@ -15,13 +15,21 @@
 // histogram the wave tracks exact counts #{x < p} at three pivots: the
 // current median m, the lower edge m - MAD and the upper edge m + MAD + 1;
 // ballots update them for every inserted/removed sample, in or out of the
-// histogram's range. The common query reads 64 bins around each pivot, one
-// bin per lane, and finds the new median and MAD with three wave prefix sums
-// and two lane shuffles. When a quantity moves further than the 64-bin
-// windows, a full scan of the histogram answers; when it leaves the histogram
-// range the window is recounted around the exact median (radix select over
-// the window in global memory), and data too spread for any placement of the
-// histogram is answered block by block by radix select.
+// histogram's range. The common query reads 16 bins around each pivot and
+// finds the new median and MAD with one row-local prefix sum and two lane
+// shuffles. When a quantity moves further, a walk of 64 bins a step from the
+// old pivots answers; when it leaves the histogram the window is recounted
+// about the median of a sample of it; and data too spread for any placement
+// of the histogram are answered block by block by radix select.
+//
+// Bound by instruction issue and, with few chains, by the serial chain of one
+// block (about 1 us alone): interior blocks, where 64 samples enter and 64
+// leave, run without clamps or lane masks (about 87 vector and as many scalar
+// instructions a block; 112 and 95 with them). 1024 x 2^20, window 16384,
+// drift period 8192: 4.91 -> 4.25 ms; 64 x 16384, window 4096 (the median
+// moves 60 values a block; answered by whole-histogram scans and recounts
+// before the walk): 2.44 -> 0.066 ms with the shorter chains that the cheap
+// recount allows.
 #include "sps_chain.h"
 
 namespace sps {
@@ -30,7 +38,7 @@ namespace {
 
 template <int NB, int WPG, bool VIRT, bool LEAD>
 __global__ __launch_bounds__(64 * WPG) void k_block_stats(StatsArgs a) {
-  __shared__ uint32_t hist[WPG][NB / 2];
+  __shared__ __align__(16) uint32_t hist[WPG][NB / 2];
   // wave index made uniform: the chain's bookkeeping then runs on the scalar
   // unit beside the vector work of the other waves
   const int wave = readfirst(threadIdx.x >> 6);
@@ -44,7 +52,7 @@ __global__ __launch_bounds__(64 * WPG) void k_block_stats(StatsArgs a) {
 // are gulps of streams (rows read through their histories).
 template <int NB, int WPG, bool VIRT, bool LEAD>
 __global__ __launch_bounds__(64 * WPG) void k_block_stats_batch(BatchStats B) {
-  __shared__ uint32_t hist[WPG][NB / 2];
+  __shared__ __align__(16) uint32_t hist[WPG][NB / 2];
   const int wave = threadIdx.x >> 6;
   const int lane = lane_id();
   while (true) {

@@ -31,6 +31,21 @@ __device__ __forceinline__ int readlane(int v, int l) { return __builtin_amdgcn_
 
 __device__ __forceinline__ int readfirst(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
+// Pointers to device memory by address space: a pointer that a kernel reads
+// from memory (a batch's item table) is generic to the compiler, and its
+// accesses would be flat ones, which also wait in the LDS counter.
+typedef __attribute__((address_space(1))) const float gbl_f32;
+typedef __attribute__((address_space(1))) int32_t gbl_i32;
+typedef __attribute__((address_space(1))) uint32_t gbl_u32;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(1))) const f32x4 gbl_f32x4;
+
+__device__ __forceinline__ gbl_f32* uniform_ptr(gbl_f32* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  return reinterpret_cast<gbl_f32*>((uint64_t)(uint32_t)readfirst((int)(uint32_t)v) |
+                                    ((uint64_t)(uint32_t)readfirst((int)(v >> 32)) << 32));
+}
+
 // Orders this wave's LDS accesses: everything before is complete before
 // anything after is issued.
 __device__ __forceinline__ void wave_lds_fence() {
