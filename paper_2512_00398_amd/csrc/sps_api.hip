@@ -7,6 +7,7 @@
 #include <new>
 #include <vector>
 
+#include "sps_dedisp_layout.h"
 #include "sps_internal.h"
 
 struct sps_plan {
@@ -1870,11 +1871,10 @@ void sps_cluster_destroy(sps_clusterer* k) {
 // ---------------------------------------------------------------- dedispersion
 
 struct sps_dedisp {
-  int32_t nchan, ndm, ndm_pad, dd, ngroups;
+  int32_t nchan, ndm, max_delay;
   int64_t nsamp_in, nsamp_out;
-  void* d_mem;               // one allocation: span table, then offsets
-  sps::DedispSpan* d_span;   // [nchan][ngroups]
-  int32_t* d_base;           // [nchan][ndm_pad]
+  sps::DedispShape shape;
+  int32_t* d_rec;            // the shape's records
   hipEvent_t done;           // end of the last run's work (destroy waits for it)
   bool pending;
 };
@@ -1882,22 +1882,6 @@ struct sps_dedisp {
 namespace {
 
 constexpr double kDispersionConst = 4.148808e3;  // MHz^2 pc^-1 cm^3 s
-
-// Largest spread of the delays of `dd` consecutive trials in any channel.
-int64_t delay_spread(const std::vector<int32_t>& dt, int32_t nchan, int32_t ndm_pad, int32_t dd) {
-  int64_t spread = 0;
-  for (int32_t f = 0; f < nchan; ++f)
-    for (int32_t g = 0; g < ndm_pad; g += dd) {
-      const int32_t* p = &dt[(size_t)f * ndm_pad + g];
-      int32_t lo = p[0], hi = p[0];
-      for (int32_t j = 1; j < dd; ++j) {
-        lo = std::min(lo, p[j]);
-        hi = std::max(hi, p[j]);
-      }
-      spread = std::max<int64_t>(spread, (int64_t)hi - lo);
-    }
-  return spread;
-}
 
 }  // namespace
 
@@ -1954,41 +1938,9 @@ static sps_dedisp* dedisp_create(int32_t nchan, int64_t nsamp_in, int32_t ndm, c
     fail(SPS_ERR_INVALID_ARG);
     return nullptr;
   }
-  // trials per workgroup: the most whose delays fit the LDS staging in every channel
-  const int64_t room = 4LL * (sps::kDedispSpanWords - 1) - 1030;
-  int32_t dd = 16;
-  std::vector<int32_t> dt;
-  int32_t ndm_pad = 0;
-  for (;; dd /= 2) {
-    ndm_pad = (ndm + dd - 1) / dd * dd;
-    dt.assign((size_t)nchan * ndm_pad, 0);
-    for (int32_t f = 0; f < nchan; ++f)
-      for (int32_t d = 0; d < ndm_pad; ++d)
-        dt[(size_t)f * ndm_pad + d] = delays[(size_t)std::min(d, ndm - 1) * nchan + f];
-    if (dd == 1 || delay_spread(dt, nchan, ndm_pad, dd) <= room) break;
-  }
-  // Per (channel, trial group): the staged span at time tile 0 (a tile
-  // starts a multiple of 4 bytes later, so only the first word moves) and
-  // each trial's byte offset into it.
-  const int32_t ngroups = ndm_pad / dd;
-  std::vector<sps::DedispSpan> span((size_t)nchan * ngroups);
-  std::vector<int32_t> base((size_t)nchan * ndm_pad);
-  for (int32_t f = 0; f < nchan; ++f)
-    for (int32_t g = 0; g < ngroups; ++g) {
-      const int32_t* p = &dt[(size_t)f * ndm_pad + (size_t)g * dd];
-      int32_t lo = p[0], hi = p[0];
-      for (int32_t j = 1; j < dd; ++j) {
-        lo = std::min(lo, p[j]);
-        hi = std::max(hi, p[j]);
-      }
-      const int64_t src0 = (int64_t)f * nsamp_in + lo;  // first byte needed at tile 0
-      const int32_t sh0 = (int32_t)(src0 & 3);
-      sps::DedispSpan& sg = span[(size_t)f * ngroups + g];
-      sg.w0 = src0 >> 2;
-      sg.nw = (sh0 + (hi - lo) + 1024 + 3) / 4 + 1;  // <= kDedispSpanWords by the choice of dd
-      sg.pad = 0;
-      for (int32_t j = 0; j < dd; ++j) base[(size_t)f * ndm_pad + (size_t)g * dd + j] = sh0 + (p[j] - lo);
-    }
+  sps::DedispShape shape = sps::dedisp_choose(nchan, ndm, nsamp_in - maxd, delays);
+  std::vector<int32_t> rec;
+  sps::dedisp_records(nchan, ndm, nsamp_in, delays, shape, rec);
   sps_dedisp* k = new (std::nothrow) sps_dedisp;
   if (!k) {
     fail(SPS_ERR_OOM);
@@ -1996,31 +1948,27 @@ static sps_dedisp* dedisp_create(int32_t nchan, int64_t nsamp_in, int32_t ndm, c
   }
   k->nchan = nchan;
   k->ndm = ndm;
-  k->ndm_pad = ndm_pad;
-  k->dd = dd;
-  k->ngroups = ngroups;
+  k->max_delay = maxd;
+  k->shape = shape;
   k->nsamp_in = nsamp_in;
   k->nsamp_out = nsamp_in - maxd;
-  k->d_mem = nullptr;
+  k->d_rec = nullptr;
   k->pending = false;
   if (hipEventCreateWithFlags(&k->done, hipEventDisableTiming) != hipSuccess) {
     delete k;
     fail(SPS_ERR_HIP);
     return nullptr;
   }
-  const size_t span_bytes = span.size() * sizeof(sps::DedispSpan), base_bytes = base.size() * sizeof(int32_t);
-  if (hipMalloc(&k->d_mem, span_bytes + base_bytes) != hipSuccess) {
+  const size_t bytes = rec.size() * sizeof(int32_t);
+  if (hipMalloc(reinterpret_cast<void**>(&k->d_rec), bytes) != hipSuccess) {
     (void)hipGetLastError();
     (void)hipEventDestroy(k->done);
     delete k;
     fail(SPS_ERR_OOM);
     return nullptr;
   }
-  k->d_span = static_cast<sps::DedispSpan*>(k->d_mem);
-  k->d_base = reinterpret_cast<int32_t*>(static_cast<char*>(k->d_mem) + span_bytes);
-  if (hipMemcpy(k->d_span, span.data(), span_bytes, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(k->d_base, base.data(), base_bytes, hipMemcpyHostToDevice) != hipSuccess) {
-    (void)hipFree(k->d_mem);
+  if (hipMemcpy(k->d_rec, rec.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
+    (void)hipFree(k->d_rec);
     (void)hipEventDestroy(k->done);
     delete k;
     fail(SPS_ERR_HIP);
@@ -2041,23 +1989,26 @@ int64_t sps_dedisp_nsamp_out(const sps_dedisp* k) {
 int sps_dedisp_run(sps_dedisp* k, const uint8_t* d_fil, hipStream_t stream, float* d_out) {
   if (!k || !d_fil || !d_out || (reinterpret_cast<uintptr_t>(d_fil) & 3u)) return fail(SPS_ERR_INVALID_ARG);
   sps::DedispArgs a;
-  a.fil32 = reinterpret_cast<const uint32_t*>(d_fil);
+  a.fil = d_fil;
   a.ld = k->nsamp_in;
   a.total_bytes = (int64_t)k->nchan * k->nsamp_in;
-  a.nfull = a.total_bytes / 4;
   a.nchan = k->nchan;
   a.ndm = k->ndm;
-  a.ndm_pad = k->ndm_pad;
   a.nsamp_out = (int32_t)k->nsamp_out;
-  a.dd = k->dd;
-  a.ngroups = k->ngroups;
-  const int64_t ntime = (k->nsamp_out + 1023) / 1024;
+  a.max_delay = k->max_delay;
+  a.gch = k->shape.gch;
+  a.nsub = k->shape.nsub;
+  a.tile = k->shape.tile;
+  a.trials = k->shape.trials;
+  a.ngroups = k->shape.ngroups;
+  const int64_t ntime = (k->nsamp_out + a.tile - 1) / a.tile;
   const int64_t ntiles = ntime * a.ngroups;
   if (ntiles > (int64_t)INT32_MAX - 8) return fail(SPS_ERR_INVALID_ARG);
   a.ntiles = (int32_t)ntiles;
   a.per_xcd = (int32_t)((ntiles + 7) / 8);
-  a.span = k->d_span;
-  a.base = k->d_base;
+  a.rec_words = k->shape.rec_words;
+  a.lds_blocks = k->shape.lds_blocks;
+  a.rec = k->d_rec;
   a.out = d_out;
   if (sps::launch_dedisp(a, stream) != hipSuccess) return fail(SPS_ERR_HIP);
   if (hipEventRecord(k->done, stream) != hipSuccess) return fail(SPS_ERR_HIP);
@@ -2109,7 +2060,7 @@ void sps_dedisp_destroy(sps_dedisp* k) {
   if (!k) return;
   if (k->pending) (void)hipEventSynchronize(k->done);
   (void)hipEventDestroy(k->done);
-  if (k->d_mem) (void)hipFree(k->d_mem);
+  if (k->d_rec) (void)hipFree(k->d_rec);
   delete k;
 }
 

@@ -87,32 +87,41 @@ struct WidthStatsArgs {
   int32_t* mad;        // [rows][nw] MAD_w
 };
 
-// Incoherent dedispersion: words of LDS staging per channel span (8 KiB;
-// four spans per workgroup).
-constexpr int kDedispSpanWords = 2048;
-
-// Staged span of one channel for one trial group, at time tile 0 (tile t
-// starts 256 t words later): first 4-byte word and word count.
-struct DedispSpan {
-  int64_t w0;
-  int32_t nw;
-  int32_t pad;
-};
+// Incoherent dedispersion. Channels are taken in subbands of `gch`
+// neighbouring ones and trials in groups; per (group, subband) a record of
+// `rec_words` int32 holds
+//   [0]          blocks of kDedispBlock subband samples that the group needs
+//   [1 + j / 2]  trial j's first subband sample, as a byte offset in LDS (the half j & 1)
+//   [kDedispHead + gch*b + i]  block b, the sample of channel i of the subband
+//                that its first element sums at time tile 0: the 4-byte word
+//                of the row that holds it (row f starts at word f * ld / 4)
+//                and, in the top two bits, its byte in the word
+// Every record has at least kDedispAhead blocks (repeats of the last).
+constexpr int kDedispMaxTrials = 32;  // trials per group (workgroup)
+constexpr int kDedispMaxGch = 4;      // channels per subband
+constexpr int kDedispBlock = 252;     // subband samples built by one wave at a time
+constexpr int kDedispHead = 1 + kDedispMaxTrials / 2;
+constexpr int kDedispAhead = 24;
+// bytes of one copy of `blocks` blocks of 16-bit samples; the sums read up to
+// 16 samples past the last block
+constexpr int dedisp_copy_bytes(int blocks) { return blocks * 2 * kDedispBlock + 40; }
 
 struct DedispArgs {
-  const uint32_t* fil32;  // filterbank bytes [nchan][ld], 4-byte aligned
+  const uint8_t* fil;     // filterbank bytes [nchan][ld], 4-byte aligned
   int64_t ld;             // row stride in bytes (= nsamp_in)
-  int64_t nfull;          // whole 4-byte words in the filterbank
   int64_t total_bytes;    // nchan * ld
-  int32_t nchan, ndm, ndm_pad, nsamp_out;
-  int32_t dd;             // trials per workgroup (16, 8, 4, 2 or 1)
-  int32_t ngroups;        // ndm_pad / dd
+  int32_t nchan, ndm, nsamp_out;
+  int32_t max_delay;
+  int32_t gch;            // channels per subband (1 .. kDedispMaxGch)
+  int32_t nsub;           // subbands
+  int32_t tile;           // output samples per workgroup (4 or 2 blocks)
+  int32_t trials;         // trials per workgroup (32, 16 or 8)
+  int32_t ngroups;        // trial groups
   int32_t ntiles;         // ngroups * time tiles
   int32_t per_xcd;        // tiles per XCD (grid = 8 * per_xcd)
-  const DedispSpan* span; // [nchan][ngroups]
-  // per channel f and trial d: byte offset of the trial's first sample in its
-  // group's staged span (trials past ndm repeat the last)
-  const int32_t* base;    // [nchan][ndm_pad]
+  int32_t rec_words;
+  int32_t lds_blocks;     // most blocks of any record (LDS: 2 buffers of 2 copies)
+  const int32_t* rec;     // [ngroups][nsub][rec_words]
   float* out;             // [ndm][nsamp_out]
 };
 
