@@ -1805,9 +1805,9 @@ sps_clusterer* sps_cluster_create(uint32_t max_cands) {
     off = (off + bytes + 255) & ~(size_t)255;
     return at;
   };
-  const size_t o_sorted = take(16 * n), o_parent = take(4 * n), o_members = take(4 * n), o_snr = take(4 * n);
+  const size_t o_sorted = take(16 * n), o_parent = take(4 * n), o_members = take(4 * n);
   const size_t o_slo = take(4 * n), o_shi = take(4 * n), o_dlo = take(4 * n), o_dhi = take(4 * n);
-  const size_t o_tie = take(8 * n), o_count = take(4 * cells), o_cursor = take(4 * cells);
+  const size_t o_tie = take(8 * n), o_count = take(4 * cells);
   const size_t o_bsum = take(4 * tiles), o_geo = take(32);
   sps_clusterer* k = new (std::nothrow) sps_clusterer;
   if (!k) {
@@ -1833,14 +1833,12 @@ sps_clusterer* sps_cluster_create(uint32_t max_cands) {
   k->s.sorted = reinterpret_cast<sps_cand*>(b + o_sorted);
   k->s.parent = reinterpret_cast<int32_t*>(b + o_parent);
   k->s.members = reinterpret_cast<uint32_t*>(b + o_members);
-  k->s.snrbits = reinterpret_cast<uint32_t*>(b + o_snr);
   k->s.slo = reinterpret_cast<int32_t*>(b + o_slo);
   k->s.shi = reinterpret_cast<int32_t*>(b + o_shi);
   k->s.dlo = reinterpret_cast<uint32_t*>(b + o_dlo);
   k->s.dhi = reinterpret_cast<uint32_t*>(b + o_dhi);
   k->s.tie = reinterpret_cast<unsigned long long*>(b + o_tie);
   k->s.count = reinterpret_cast<uint32_t*>(b + o_count);
-  k->s.cursor = reinterpret_cast<uint32_t*>(b + o_cursor);
   k->s.bsum = reinterpret_cast<uint32_t*>(b + o_bsum);
   k->s.geo = reinterpret_cast<int32_t*>(b + o_geo);
   ok();

@@ -241,16 +241,14 @@ struct BatchDetect {
 constexpr int kClusterCells = 1 << 22;  // time cells of the bucketing
 struct ClusterScratch {
   sps_cand* sorted;   // [cap] candidates in bucket order
-  int32_t* parent;    // [cap] union-find over positions (parent <= position)
-  uint32_t* members;  // [cap] per root: member count
-  uint32_t* snrbits;  //        largest S/N (float bits)
+  int32_t* parent;    // [cap] rank in the cell, then union-find over positions (parent <= position)
+  uint32_t* members;  // [cap] per root: member count (0 for positions that were never a root)
   int32_t* slo;       //        sample extent
   int32_t* shi;
   uint32_t* dlo;      //        DM extent
   uint32_t* dhi;
-  unsigned long long* tie;  // [cap] per root: smallest (dm, width, sample) key at the largest S/N
+  unsigned long long* tie;  // [cap] per root: S/N bits and position of the best member
   uint32_t* count;    // [kClusterCells + 2] cell counts, then cell starts
-  uint32_t* cursor;   // [kClusterCells + 2] scatter cursors
   uint32_t* bsum;     // [kClusterCells / 1024 + 1] scan tile totals
   int32_t* geo;       // [8] cell geometry (sample and DM ranges, cell sizes)
 };
