@@ -144,15 +144,23 @@ __global__ __launch_bounds__(256) void k_cluster_range(const sps_cand* c, uint32
   }
 }
 
-__global__ void k_cluster_fill(ClusterScratch s) {
+__global__ void k_cluster_begin(ClusterScratch s, uint32_t* nout) {
+  if (threadIdx.x != 0) return;
+  s.geo[0] = INT_MAX;
+  s.geo[1] = INT_MIN;
+  s.geo[4] = INT_MAX;
+  s.geo[5] = INT_MIN;
+  *nout = 0u;
+}
+
+// Entries of `count` in use: the cells and two more (a cell's range ends at
+// the next one's start). The kernels over them are launched for all cells and
+// leave the rest alone: a short or narrow set has few.
+__device__ __forceinline__ int used_cells(const ClusterScratch& s) { return s.geo[3] * s.geo[7] + 2; }
+
+__global__ void k_cluster_clear(ClusterScratch s) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < kClusterCells + 2) s.count[i] = 0u;
-  if (i == 0) {
-    s.geo[0] = INT_MAX;
-    s.geo[1] = INT_MIN;
-    s.geo[4] = INT_MAX;
-    s.geo[5] = INT_MIN;
-  }
+  if (i < used_cells(s)) s.count[i] = 0u;
 }
 
 // Cell sizes: at least dm_tol + 1 trials and time_tol + 1 samples, and large
@@ -199,7 +207,7 @@ __global__ void k_cluster_count(const sps_cand* c, uint32_t n, ClusterScratch s)
   if (i < n) s.parent[i] = (int)atomicAdd(&s.count[cell_of(s, c[i])], 1u);
 }
 
-// Exclusive prefix sums of count[0 .. kClusterCells + 2), in place, in three
+// Exclusive prefix sums of the used part of count[0 .. kClusterCells + 2), in place, in three
 // passes: 1024 entries per workgroup, then the workgroup totals, then the
 // offsets added back.
 constexpr int kScanTile = 1024;
@@ -208,10 +216,12 @@ constexpr int kScanTiles = (kClusterCells + 2 + kScanTile - 1) / kScanTile;
 __global__ __launch_bounds__(256) void k_scan_tiles(ClusterScratch s) {
   __shared__ uint32_t wsum[4];
   const int t = threadIdx.x, lane = lane_id(), wave = t >> 6;
+  const int used = used_cells(s);
+  if ((int)blockIdx.x * kScanTile >= used) return;  // whole workgroup
   const int base = blockIdx.x * kScanTile + 4 * t;
   uint32_t v[4];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) v[q] = base + q < kClusterCells + 2 ? s.count[base + q] : 0u;
+  for (int q = 0; q < 4; ++q) v[q] = base + q < used ? s.count[base + q] : 0u;
   const uint32_t own = v[0] + v[1] + v[2] + v[3];
   const uint32_t incl = (uint32_t)wave_scan_incl((int)own);
   if (lane == 63) wsum[wave] = incl;
@@ -221,7 +231,7 @@ __global__ __launch_bounds__(256) void k_scan_tiles(ClusterScratch s) {
   uint32_t run = off + incl - own;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    if (base + q < kClusterCells + 2) s.count[base + q] = run;
+    if (base + q < used) s.count[base + q] = run;
     run += v[q];
   }
   if (t == 255) s.bsum[blockIdx.x] = off + incl;
@@ -231,16 +241,17 @@ __global__ __launch_bounds__(1024) void k_scan_totals(ClusterScratch s) {
   __shared__ uint32_t wsum[16];
   __shared__ uint32_t carry;
   const int t = threadIdx.x, lane = lane_id(), wave = t >> 6;
+  const int tiles = (used_cells(s) + kScanTile - 1) / kScanTile;
   if (t == 0) carry = 0u;
   __syncthreads();
-  for (int b0 = 0; b0 < kScanTiles; b0 += 1024) {
-    const uint32_t own = b0 + t < kScanTiles ? s.bsum[b0 + t] : 0u;
+  for (int b0 = 0; b0 < tiles; b0 += 1024) {
+    const uint32_t own = b0 + t < tiles ? s.bsum[b0 + t] : 0u;
     const uint32_t incl = (uint32_t)wave_scan_incl((int)own);
     if (lane == 63) wsum[wave] = incl;
     __syncthreads();
     uint32_t off = carry;
     for (int w = 0; w < wave; ++w) off += wsum[w];
-    if (b0 + t < kScanTiles) s.bsum[b0 + t] = off + incl - own;
+    if (b0 + t < tiles) s.bsum[b0 + t] = off + incl - own;
     __syncthreads();
     if (t == 1023) carry = off + incl;
     __syncthreads();
@@ -249,9 +260,7 @@ __global__ __launch_bounds__(1024) void k_scan_totals(ClusterScratch s) {
 
 __global__ void k_scan_add(ClusterScratch s) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < kClusterCells + 2) {
-    s.count[i] += s.bsum[i / kScanTile];
-  }
+  if (i < used_cells(s)) s.count[i] += s.bsum[i / kScanTile];
 }
 
 // Records in bucket order.
@@ -544,12 +553,12 @@ hipError_t launch_cluster(const sps_cand* c, uint32_t n, int tt, int dt, int wt,
                           sps_cluster_rec* out, uint32_t* nout, hipStream_t st) {
   const dim3 b(256);
   const dim3 gc((kClusterCells + 2 + 255) / 256);
-  hipLaunchKernelGGL(k_cluster_fill, gc, b, 0, st, s);
-  if (launch_zero_u32(nout, 1, st) != hipSuccess) return hipGetLastError();
+  hipLaunchKernelGGL(k_cluster_begin, dim3(1), dim3(64), 0, st, s, nout);
   if (n > 0) {
     const dim3 gn((n + 255) / 256);
     hipLaunchKernelGGL(k_cluster_range, dim3(std::min(256u, (n + 1023) / 1024)), b, 0, st, c, n, s);
     hipLaunchKernelGGL(k_cluster_geometry, dim3(1), dim3(64), 0, st, tt, dt, s);
+    hipLaunchKernelGGL(k_cluster_clear, gc, b, 0, st, s);
     hipLaunchKernelGGL(k_cluster_count, gn, b, 0, st, c, n, s);
     hipLaunchKernelGGL(k_scan_tiles, dim3(kScanTiles), b, 0, st, s);
     hipLaunchKernelGGL(k_scan_totals, dim3(1), dim3(1024), 0, st, s);
