@@ -65,6 +65,11 @@ int ok() {
 }
 
 constexpr int kDetectStep = 1024;
+// Longer detection segments only where a CU has no more than four: with many
+// rounds, short ones even out better (1024 x 2^20, widths to 4096, fast and slow
+// drift: 65536 positions 8.98 and 4.18 ms, 131072 9.31 and 4.48, whole rows 9.71
+// and 4.19).
+constexpr int64_t kLongSegment = 65536;
 
 // Waves of the statistics kernel that the chip holds with 32 KB of histograms
 // per workgroup of four (256 CUs x 4 workgroups).
@@ -154,10 +159,12 @@ void stats_segments_clipped(const sps_plan* p, int64_t nb, int32_t& seg, int32_t
 // Positions per detection segment for rows of `npos` positions (tuning only).
 int detect_seg_for(const sps_plan* p, int64_t npos) {
   int64_t seg = p->detect_seg;
-  if (seg <= 0) {
-    // ~8192 workgroups; each segment >= 4 x max_width so the halo stays small
+  const bool chosen = seg > 0;
+  if (!chosen) {
+    // about 8192 workgroups, more of a large block; each segment >= 4 x max_width
+    // so the halo stays small
     const int64_t total = (int64_t)p->ndm * npos;
-    seg = total / 8192;
+    seg = std::min<int64_t>(total / 8192, kLongSegment);
     seg = std::max<int64_t>(seg, 4LL * p->max_width);
   }
   seg = ((seg + kDetectStep - 1) / kDetectStep) * kDetectStep;
@@ -165,7 +172,28 @@ int detect_seg_for(const sps_plan* p, int64_t npos) {
   const int64_t nmax = (npos + kDetectStep - 1) / kDetectStep * kDetectStep;
   if (seg > nmax) seg = nmax;
   if (seg < kDetectStep) seg = kDetectStep;
-  return (int)seg;
+  if (chosen) return (int)seg;
+  // From there on, the segment with the fewest rounds of steps: a segment
+  // takes its own steps and its halo's, four workgroups fill a CU, fewer run
+  // their steps somewhat faster, and many even out segments of unlike cost
+  // (us, detection, 4 x max_width and the choice: 256 x 131072, widths to 4096:
+  // 194 and 163; 256 x 65536, to 1024: 126 and 92; 333 x 100003, to 512: 192
+  // and 158).
+  int64_t best = seg;
+  double best_t = 0.0;
+  for (int64_t per_row = (npos + seg - 1) / seg; per_row >= 1; --per_row) {
+    const int64_t s = ((npos + per_row - 1) / per_row + kDetectStep - 1) / kDetectStep * kDetectStep;
+    const int64_t wgs = (int64_t)p->ndm * ((npos + s - 1) / s);
+    const double per_cu = (double)((wgs + 255) / 256);
+    if (s > kLongSegment && per_cu > 4.0 && best_t > 0.0) continue;
+    const double steps = (double)(s / kDetectStep + (p->max_width + 64 + kDetectStep - 1) / kDetectStep);
+    const double t = steps * (per_cu <= 4.0 ? 0.4 + 0.15 * per_cu : std::ceil(per_cu / 4.0)) * (1.0 + 0.4 / per_cu);
+    if (best_t == 0.0 || t < best_t) {
+      best_t = t;
+      best = s;
+    }
+  }
+  return (int)best;
 }
 
 int auto_detect_seg(const sps_plan* p) { return detect_seg_for(p, p->nsamp); }
@@ -1475,7 +1503,7 @@ int sps_batch_search(sps_batch* b, const sps_batch_item* items, int32_t n, hipSt
     if (b->stats_seg == 0)
       shorten_first_segment(s.nblocks, std::min<int64_t>(it.baseline_len, it.nsamp), s.stats_nseg, s.stats_seg,
                             s.stats_head);
-    int64_t dseg = b->detect_seg > 0 ? b->detect_seg : std::max<int64_t>(total_samples / 8192, 4LL * it.max_width);
+    int64_t dseg = b->detect_seg > 0 ? b->detect_seg : std::max<int64_t>(std::min<int64_t>(total_samples / 8192, kLongSegment), 4LL * it.max_width);
     dseg = (dseg + kDetectStep - 1) / kDetectStep * kDetectStep;
     const int64_t nmax = std::max<int64_t>(kDetectStep, (it.nsamp + kDetectStep - 1) / kDetectStep * kDetectStep);
     dseg = std::max<int64_t>(kDetectStep, std::min<int64_t>(dseg, nmax));

@@ -231,12 +231,17 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
   __shared__ sps_cand cbuf[2][kCbuf];
   __shared__ __align__(16) uint32_t wtot[2][4];
   __shared__ uint32_t step_mask, flush_n, flush_base;
+  __shared__ uint32_t carry_open;  // widths whose carried run is open, or that have had no position yet
   __shared__ uint32_t cbuf_n[2];
 
   const int tid = threadIdx.x, lane = lane_id();
   const int wave = readfirst(tid >> 6);
   const int row = task / A.nseg;
-  const int seg = task - row * A.nseg;
+  // Segments rotate with the row: workgroups go to the XCDs in turn, and with
+  // a multiple of 8 segments per row one XCD would get the same stretch of
+  // time of every row (1024 x 2^20, a slow drift, 16 segments:
+  // 6.06 -> 4.18 ms).
+  const int seg = (task - row * A.nseg + row) % A.nseg;
   const int N = A.N;
   const int s0 = A.seg_base + seg * A.seg_len;
   const int s1 = min(N, s0 + A.seg_len);
@@ -311,7 +316,7 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
     carry[tid] = rs_empty();
     s_sqw[tid] = A.sqrtw[tid];
   }
-  if (tid == 0) { cbuf_n[0] = 0u; cbuf_n[1] = 0u; }
+  if (tid == 0) { cbuf_n[0] = 0u; cbuf_n[1] = 0u; carry_open = (1u << nw) - 1u; }
   uint32_t carryP = 0;  // P at the step's first sample
   __syncthreads();
 
@@ -372,6 +377,9 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
 #pragma unroll
             for (int q = 0; q < 4; ++q) pe[q] = ring[(eg + 64 * q + lane) & (kRing - 1)];
           }
+          const int vhi = min(e_seg + w - 1, e_row), vlo = max(w, max(e_lo0, e_lo1 + w));
+          if (!CLEAN && (vhi < eg || vlo > eg + 255)) continue;  // none of the wave's window ends
+          const bool whole = CLEAN || (vlo <= eg && vhi >= eg + 255);
           const int4 T4 = *reinterpret_cast<const int4*>(&tlo[j][4 * wave]);
           uint64_t acc = 0ull;
 #pragma unroll
@@ -379,14 +387,9 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
             const int e0 = eg + 64 * q;
             const int S = (int)(pe[q] - ring[(e0 - w + lane) & (kRing - 1)]);
             const int T = q == 0 ? T4.x : q == 1 ? T4.y : q == 2 ? T4.z : T4.w;
-            const uint64_t hit = ballot(S > T);
-            if (CLEAN) {
-              acc |= hit;
-            } else {
-              const int vhi = min(e_seg + w - 1, e_row);
-              const int vlo = max(w, max(e_lo0, e_lo1 + w));
-              acc |= hit & lane_range(vlo - e0, vhi - e0);
-            }
+            uint64_t hit = ballot(S > T);
+            if (!CLEAN && !whole) hit &= lane_range(vlo - e0, vhi - e0);
+            acc |= hit;
           }
           flagged |= acc ? (1u << j) : 0u;
         }
@@ -406,13 +409,14 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
             cur_sh4 = sh;
             pe4 = *reinterpret_cast<const uint4*>(&ring[e4 & (kRing - 1)]);
           }
+          const int vhi = min(e_seg + w - 1, e_row), vlo = max(w, max(e_lo0, e_lo1 + w));
+          if (!CLEAN && (vhi < eg || vlo > eg + 255)) continue;  // none of the wave's window ends
+          const bool whole = CLEAN || (vlo <= eg && vhi >= eg + 255);
           const uint4 pw4 = *reinterpret_cast<const uint4*>(&ring[(e4 - w) & (kRing - 1)]);
           const int T = tlo[j][4 * wave + gq];
           int d0 = (int)(pe4.x - pw4.x), d1 = (int)(pe4.y - pw4.y);
           int d2 = (int)(pe4.z - pw4.z), d3 = (int)(pe4.w - pw4.w);
-          if (!CLEAN) {
-            const int vhi = min(e_seg + w - 1, e_row);
-            const int vlo = max(w, max(e_lo0, e_lo1 + w));
+          if (!CLEAN && !whole) {
             d0 = (e4 >= vlo && e4 <= vhi) ? d0 : INT_MIN;
             d1 = (e4 + 1 >= vlo && e4 + 1 <= vhi) ? d1 : INT_MIN;
             d2 = (e4 + 2 >= vlo && e4 + 2 <= vhi) ? d2 : INT_MIN;
@@ -423,7 +427,7 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
           const int dm = max(max(d0, d1), max(d2, d3));
           const uint64_t hit = ballot(dm > T);
           flagged |= hit ? (1u << j) : 0u;
-          if (CLEAN && hit == ~0ull) {
+          if (whole && hit == ~0ull) {
             // Every lane has a candidate: if every one of the wave's 256
             // positions is above for sure, its 4 groups are single full runs
             // and their summaries are written here (the run pass skips them).
@@ -572,12 +576,17 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
         st.tq = tq;
         cj = rs_combine_p(cj, st, pe[2]);
         pe[2].f = pe[2].f && owner;
-        if (owner) carry[j] = cj;
+        if (owner) {
+          carry[j] = cj;
+          if (cj.flags & (kTail | kFull)) atomicOr(&carry_open, 1u << j);
+          else atomicAnd(&carry_open, ~(1u << j));
+        }
         emit_batch(pe, em, lane);
       }
     }
-    for (int j = wave; j < nw; j += 4) {
-      if ((smask >> j) & 1u) continue;
+    // (each width's bit is read and written by one wave of the step only)
+    for (uint32_t todo = (uint32_t)readfirst((int)carry_open) & ~smask & (0x1111u << wave); todo; todo &= todo - 1u) {
+      const int j = __builtin_ctz(todo);
       const int w = 1 << j, sh = group_shift(w);
       const Emitter em{cbuf[buf], &cbuf_n[buf], A.cands, A.ncand, A.cap, dm, (uint32_t)w, lane == 0,
                        A.sample_offset};
@@ -597,6 +606,7 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
           dirty = true;
         }
         if (dirty && lane == 0) carry[j] = cj;
+        if (lane == 0) atomicAnd(&carry_open, ~(1u << j));  // closed: nothing above
       }
     }
   }
