@@ -67,8 +67,8 @@ int ok() {
 constexpr int kDetectStep = 1024;
 // Longer detection segments only where a CU has no more than four: with many
 // rounds, short ones even out better (1024 x 2^20, widths to 4096, fast and slow
-// drift: 65536 positions 8.98 and 4.18 ms, 131072 9.31 and 4.48, whole rows 9.71
-// and 4.19).
+// drift: 65536 positions 6.52 and 2.98 ms, 131072 6.42 and 3.25, 262144 6.69
+// and 3.31, whole rows 7.85 and 3.30).
 constexpr int64_t kLongSegment = 65536;
 
 // Waves of the statistics kernel that the chip holds with 32 KB of histograms

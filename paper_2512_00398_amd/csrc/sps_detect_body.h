@@ -15,7 +15,10 @@ namespace sps {
 namespace {
 
 constexpr int kC = 1024;                 // samples (window ends) per step
-constexpr int kRing = 8192;              // ring entries, >= kC + 64 + max width
+constexpr int kRing = 5376;              // ring entries: >= kC + 64 + max width, a multiple of 256
+constexpr int kRingCopy = 512;           // and a copy of the first 512 behind them
+constexpr int kStageWords = 2 * kCbuf * (int)(sizeof(sps_cand) / 4);  // candidates staged behind those
+constexpr int kRingWords = kRing + kRingCopy + kStageWords;
 constexpr int kGroups = kC / 64;         // 64-position groups per step and width
 
 // Best (largest S, earliest lane) of the lanes in `run`; wave-uniform result.
@@ -196,6 +199,9 @@ __device__ __forceinline__ int group_shift(int w) {
   return (64 - (sub & 63)) & 63;
 }
 
+// A ring position that may be up to a ring's length too low.
+__device__ __forceinline__ int ring_up(int i) { return i < 0 ? i + kRing : i; }
+
 // NW > 0: the number of widths is a compile-time constant (fast pass unrolled);
 // NW == 0: any number of widths.
 //
@@ -210,25 +216,36 @@ __device__ __forceinline__ int group_shift(int w) {
 //      scan in one row of 16 lanes and folded into the width's carried run
 //      (no barrier before the next A)
 // Samples, medians and MADs are fetched one step ahead of their use.
-// The prefix-sum ring of a detection workgroup (32 KB of its ~40 KB of LDS).
-// One array per kernel, whoever asks: the fused batch kernel keeps its
-// statistics histograms in it before the workgroup turns to detection.
+// The prefix-sum ring of a detection workgroup and its candidate staging (26 KB
+// of its 32 KB of LDS). One array of WORDS per kernel, whoever asks: the fused
+// batch kernel keeps its statistics histograms in it before the workgroup turns
+// to detection.
+//
+// The ring is no power of two: 5376 entries are what the widest window needs,
+// and five workgroups then fit a CU instead of the four of an 8192-entry ring
+// (1024 x 2^20 with a fast drift, 7.5 -> 6.5 ms). A wave reads 256 consecutive
+// entries, from at most 256 before its samples on at fixed distances; none of
+// these wrap, since the first 512 entries are kept a second time behind the
+// last. What wraps is one position per wave, and one per width above 256, in
+// scalar registers.
+template <int WORDS>
 __device__ __forceinline__ uint32_t* detect_ring() {
-  __shared__ __align__(16) uint32_t ring[kRing];
+  static_assert(WORDS >= kRingWords, "the ring and the copy of its first entries");
+  __shared__ __align__(16) uint32_t ring[WORDS];
   return ring;
 }
 
-template <int NW, bool VIRT>
+template <int NW, bool VIRT, int WORDS = kRingWords>
 __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task) {
   const int nw = NW > 0 ? NW : A.nw;
-  uint32_t* const ring = detect_ring();
+  uint32_t* const ring = detect_ring<WORDS>();
   __shared__ int32_t tlo[kMaxWidths][kGroups];
   __shared__ int32_t thi[kMaxWidths][kGroups];  // S > thi: above for sure (INT_MAX: never)
   __shared__ int32_t tmad[kMaxWidths][kGroups];
   __shared__ uint4 gsum[kMaxWidths][kGroups];
   __shared__ RunSum carry[kMaxWidths];
   __shared__ double s_sqw[kMaxWidths];
-  __shared__ sps_cand cbuf[2][kCbuf];
+  sps_cand(*const cbuf)[kCbuf] = reinterpret_cast<sps_cand(*)[kCbuf]>(ring + kRing + kRingCopy);
   __shared__ __align__(16) uint32_t wtot[2][4];
   __shared__ uint32_t step_mask, flush_n, flush_base;
   __shared__ uint32_t carry_open;  // widths whose carried run is open, or that have had no position yet
@@ -318,6 +335,12 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
   }
   if (tid == 0) { cbuf_n[0] = 0u; cbuf_n[1] = 0u; carry_open = (1u << nw) - 1u; }
   uint32_t carryP = 0;  // P at the step's first sample
+  int cb = 0;           // the staging buffer in use
+  int rpos = 256 * wave;  // ring position of the wave's 256 samples of the step, a multiple of 256
+  // all ones if the samples of wave 0, 1, 2 come before this wave's (kept in
+  // vector registers: as scalar conditions they would be spilled)
+  uint32_t wmask0 = wave > 0 ? ~0u : 0u, wmask1 = wave > 1 ? ~0u : 0u, wmask2 = wave > 2 ? ~0u : 0u;
+  asm volatile("" : "+v"(wmask0), "+v"(wmask1), "+v"(wmask2));
   __syncthreads();
 
   for (int c = 0; c < nsteps; ++c) {
@@ -331,12 +354,14 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
     // ---- A: ring and bounds of step c
     {
       const uint4 wt = *reinterpret_cast<const uint4*>(&wtot[buf][0]);
-      const uint32_t woff = (wave > 0 ? wt.x : 0u) + (wave > 1 ? wt.y : 0u) + (wave > 2 ? wt.z : 0u);
+      const uint32_t woff = (wt.x & wmask0) + (wt.y & wmask1) + (wt.z & wmask2);
       const uint32_t tot = wt.x + wt.y + wt.z + wt.w;
       // P[E] = sum of r over the segment's first E samples; thread tid owns
       // E = cC + 4*tid + q, so every 64 consecutive E of a wave row are one group
       const uint32_t pb = carryP + woff + incl - p3;
-      *reinterpret_cast<uint4*>(&ring[(cC + 4 * tid) & (kRing - 1)]) = make_uint4(pb, pb + p0, pb + p1, pb + p2);
+      const uint4 pv = make_uint4(pb, pb + p0, pb + p1, pb + p2);
+      *reinterpret_cast<uint4*>(&ring[rpos + 4 * lane]) = pv;
+      if (rpos < kRingCopy) *reinterpret_cast<uint4*>(&ring[kRing + rpos + 4 * lane]) = pv;
       carryP += tot;
     }
     if (tthr) {
@@ -349,20 +374,26 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
     if (tid == 0) step_mask = 0u;
     __syncthreads();  // BA
 
-    // ---- B: flush slot for step c-1's candidates; fast pass; prefix of step c+1
+    // ---- B: flush slot for the staged candidates; fast pass; prefix of step c+1
     uint32_t fl_n = 0, fl_base = 0;
     if (tid == 0) {
-      fl_n = min(cbuf_n[buf ^ 1], (uint32_t)kCbuf);
-      cbuf_n[buf ^ 1] = 0u;
-      if (fl_n) fl_base = atomicAdd(A.ncand, fl_n);
+      const uint32_t n = cbuf_n[cb];
+      if (n >= (uint32_t)kFlush) {
+        fl_n = min(n, (uint32_t)kCbuf);
+        cbuf_n[cb] = 0u;
+        fl_base = atomicAdd(A.ncand, fl_n);
+      }
     }
-    uint32_t fullmask;  // widths whose 4 groups of this wave are full runs (summaries written)
+    uint32_t fullmask = 0u;  // widths whose 4 groups of this wave are full runs (summaries written)
     // interior step: every position of every width is valid, no masks needed
     const bool clean = cC - 64 >= max(A.maxw, max(e_lo0, e_lo1 + A.maxw)) &&
                        cC + kC - 1 <= min(e_seg, e_row - A.maxw);
+    // Window ends and starts of widths to 256 lie at fixed distances from
+    // here, without a wrap (up to 512 entries on).
+    const int rback = ring_up(rpos - 256);
     {
-      uint32_t flagged = 0u;
-      fullmask = 0u;
+      uint32_t flagged = 0u;  // widths with a position above, or undecided
+      uint32_t every = 0u;    // widths with one in every lane
       auto fast = [&](auto CLEAN) {
         // widths below 8: lane l reads window end l of each of the wave's 4 groups
         int cur_shift = -1;
@@ -372,10 +403,11 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
           if (j >= nw) break;
           const int w = 1 << j, sh = group_shift(w);
           const int eg = cC - sh + 256 * wave;
+          const uint32_t* const re = ring + rback + lane + (256 - sh);
           if (sh != cur_shift) {
             cur_shift = sh;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) pe[q] = ring[(eg + 64 * q + lane) & (kRing - 1)];
+            for (int q = 0; q < 4; ++q) pe[q] = re[64 * q];
           }
           const int vhi = min(e_seg + w - 1, e_row), vlo = max(w, max(e_lo0, e_lo1 + w));
           if (!CLEAN && (vhi < eg || vlo > eg + 255)) continue;  // none of the wave's window ends
@@ -385,7 +417,7 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             const int e0 = eg + 64 * q;
-            const int S = (int)(pe[q] - ring[(e0 - w + lane) & (kRing - 1)]);
+            const int S = (int)(pe[q] - re[64 * q - w]);
             const int T = q == 0 ? T4.x : q == 1 ? T4.y : q == 2 ? T4.z : T4.w;
             uint64_t hit = ballot(S > T);
             if (!CLEAN && !whole) hit &= lane_range(vlo - e0, vhi - e0);
@@ -395,7 +427,8 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
         }
         // widths 8 and up: the group shift is a multiple of 4, so lane l reads
         // window ends 4l .. 4l+3 of the wave's 256 with one 16-byte LDS read
-        // (group l / 16)
+        // (group l / 16). No branch between the widths of an interior step:
+        // their reads are in flight together.
         int cur_sh4 = -1;
         uint4 pe4 = make_uint4(0u, 0u, 0u, 0u);
         const int gq = lane >> 4;
@@ -405,14 +438,15 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
           const int w = 1 << j, sh = group_shift(w);
           const int eg = cC - sh + 256 * wave;
           const int e4 = eg + 4 * lane;
+          const uint32_t* const re = ring + rback + 4 * lane + (256 - sh);
           if (sh != cur_sh4) {
             cur_sh4 = sh;
-            pe4 = *reinterpret_cast<const uint4*>(&ring[e4 & (kRing - 1)]);
+            pe4 = *reinterpret_cast<const uint4*>(re);
           }
           const int vhi = min(e_seg + w - 1, e_row), vlo = max(w, max(e_lo0, e_lo1 + w));
           if (!CLEAN && (vhi < eg || vlo > eg + 255)) continue;  // none of the wave's window ends
           const bool whole = CLEAN || (vlo <= eg && vhi >= eg + 255);
-          const uint4 pw4 = *reinterpret_cast<const uint4*>(&ring[(e4 - w) & (kRing - 1)]);
+          const uint4 pw4 = *reinterpret_cast<const uint4*>(w <= 256 ? re - w : ring + ring_up(rpos - w) + 4 * lane);
           const int T = tlo[j][4 * wave + gq];
           int d0 = (int)(pe4.x - pw4.x), d1 = (int)(pe4.y - pw4.y);
           int d2 = (int)(pe4.z - pw4.z), d3 = (int)(pe4.w - pw4.w);
@@ -424,40 +458,45 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
           }
           // one comparison of the largest of the four (no short-circuit: a
           // logical or lets the compiler split the load and branch)
-          const int dm = max(max(d0, d1), max(d2, d3));
-          const uint64_t hit = ballot(dm > T);
+          const uint64_t hit = ballot(max(max(d0, d1), max(d2, d3)) > T);
           flagged |= hit ? (1u << j) : 0u;
-          if (whole && hit == ~0ull) {
-            // Every lane has a candidate: if every one of the wave's 256
-            // positions is above for sure, its 4 groups are single full runs
-            // and their summaries are written here (the run pass skips them).
-            const int F = thi[j][4 * wave + gq];
-            if (ballot(min(min(d0, d1), min(d2, d3)) > F) == ~0ull) {
-              int rm = dm;  // group maximum, in every lane of the row
-              rm = max_step<0xb1>(rm);
-              rm = max_step<0x4e>(rm);
-              rm = max_step<0x141>(rm);
-              rm = max_step<0x140>(rm);
-              // first position of the maximum within the group (0..63)
-              const int kk = d0 == rm ? 0 : (d1 == rm ? 1 : (d2 == rm ? 2 : 3));
-              int pos = dm == rm ? 4 * (lane & 15) + kk : 64;
-              pos = min_step<0xb1>(pos);
-              pos = min_step<0x4e>(pos);
-              pos = min_step<0x141>(pos);
-              pos = min_step<0x140>(pos);
-              if ((lane & 15) == 0) {
-                const int g = 4 * wave + gq;
-                gsum[j][g] = make_uint4((uint32_t)(kNonEmpty | kFull | kHead) | ((uint32_t)pos << 8), (uint32_t)rm,
-                                        0u, (uint32_t)tmad[j][g]);
-              }
-              fullmask |= 1u << j;
-            }
-          }
+          every |= whole && hit == ~0ull ? (1u << j) : 0u;
         }
       };
       if (clean) fast(std::true_type{});
       else fast(std::false_type{});
       if (flagged && lane == 0) atomicOr(&step_mask, flagged);
+      // Where every lane has a candidate: if every one of the wave's 256
+      // positions is above for sure, its 4 groups are single full runs and
+      // their summaries are written here (the run pass skips them).
+      for (; every; every &= every - 1u) {
+        const int j = __builtin_ctz(every);
+        const int w = 1 << j, gq = lane >> 4, g = 4 * wave + gq;
+        const int re = rback + 256 - group_shift(w);
+        const uint4 pe4 = *reinterpret_cast<const uint4*>(&ring[re + 4 * lane]);
+        const uint4 pw4 = *reinterpret_cast<const uint4*>(&ring[ring_up(re - w) + 4 * lane]);
+        const int F = thi[j][g];
+        const int d0 = (int)(pe4.x - pw4.x), d1 = (int)(pe4.y - pw4.y);
+        const int d2 = (int)(pe4.z - pw4.z), d3 = (int)(pe4.w - pw4.w);
+        if (ballot(min(min(d0, d1), min(d2, d3)) > F) != ~0ull) continue;
+        const int dm = max(max(d0, d1), max(d2, d3));
+        int rm = dm;  // group maximum, in every lane of the row
+        rm = max_step<0xb1>(rm);
+        rm = max_step<0x4e>(rm);
+        rm = max_step<0x141>(rm);
+        rm = max_step<0x140>(rm);
+        // first position of the maximum within the group (0..63)
+        const int kk = d0 == rm ? 0 : (d1 == rm ? 1 : (d2 == rm ? 2 : 3));
+        int pos = dm == rm ? 4 * (lane & 15) + kk : 64;
+        pos = min_step<0xb1>(pos);
+        pos = min_step<0x4e>(pos);
+        pos = min_step<0x141>(pos);
+        pos = min_step<0x140>(pos);
+        if ((lane & 15) == 0)
+          gsum[j][g] = make_uint4((uint32_t)(kNonEmpty | kFull | kHead) | ((uint32_t)pos << 8), (uint32_t)rm, 0u,
+                                  (uint32_t)tmad[j][g]);
+        fullmask |= 1u << j;
+      }
     }
     if (c + 1 < nsteps) {
       prefix(c + 1, nmk, nf0, nf1, nf2, nf3);
@@ -466,33 +505,33 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
     if (tid == 0) { flush_n = fl_n; flush_base = fl_base; }
     __syncthreads();  // BB
 
-    // ---- C: copy out step c-1's candidates; run pass
-    {
-      const uint32_t n = flush_n, base = flush_base;
+    // ---- C: copy out what is flushed; run pass
+    if (const uint32_t n = (uint32_t)readfirst((int)flush_n)) {
+      const uint32_t base = flush_base;
       for (uint32_t i = tid; i < n; i += 256)
-        if (base + i < A.cap) A.cands[base + i] = cbuf[buf ^ 1][i];
+        if (base + i < A.cap) A.cands[base + i] = cbuf[cb][i];
+      cb ^= 1;  // this step's candidates go to the other buffer
     }
     const uint32_t smask = step_mask;
-    const uint32_t rmask = smask & ~fullmask;
-    for (int j = 0; j < nw; ++j) {
-      if (!((rmask >> j) & 1u)) continue;
+    for (uint32_t todo = (uint32_t)readfirst((int)smask) & ~fullmask; todo; todo &= todo - 1u) {
+      const int j = __builtin_ctz(todo);
       const int w = 1 << j, sh = group_shift(w);
       const int eg = cC - sh + 256 * wave;
       const int vhi = min(e_seg + w - 1, e_row);
       const int vlo = max(w, max(e_lo0, e_lo1 + w));
       const double sqw = A.sqrtw[j];
-      const Emitter em{cbuf[buf], &cbuf_n[buf], A.cands, A.ncand, A.cap, dm, (uint32_t)w, lane == 0,
+      const Emitter em{cbuf[cb], &cbuf_n[cb], A.cands, A.ncand, A.cap, dm, (uint32_t)w, lane == 0,
                        A.sample_offset};
       const int4 LO = *reinterpret_cast<const int4*>(&tlo[j][4 * wave]);
       const int4 HI = *reinterpret_cast<const int4*>(&thi[j][4 * wave]);  // S > HI: above for sure
       const int4 MD = *reinterpret_cast<const int4*>(&tmad[j][4 * wave]);
+      const int re = rback + 256 - sh, rw = ring_up(re - w);
       int S[4], best[4];
       bool in[4];
       uint64_t M[4], V[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int e = eg + 64 * q + lane;
-        S[q] = (int)(ring[e & (kRing - 1)] - ring[(e - w) & (kRing - 1)]);
+        S[q] = (int)(ring[re + lane + 64 * q] - ring[rw + lane + 64 * q]);
         const int lo = q == 0 ? LO.x : q == 1 ? LO.y : q == 2 ? LO.z : LO.w;
         const int hi = q == 0 ? HI.x : q == 1 ? HI.y : q == 2 ? HI.z : HI.w;
         const int mad = q == 0 ? MD.x : q == 1 ? MD.y : q == 2 ? MD.z : MD.w;
@@ -528,6 +567,7 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
       }
     }
     cur_mad = next_mad;
+    rpos = rpos + kC >= kRing ? rpos + kC - kRing : rpos + kC;
     __syncthreads();  // BC
 
     // ---- D: the 16 group summaries of each flagged width are combined in
@@ -559,7 +599,7 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
           hq = (double)(int)pk.y / den;
           tq = (double)(int)pk.z / den;
         }
-        const Emitter em{cbuf[buf], &cbuf_n[buf], A.cands, A.ncand, A.cap, dm, (uint32_t)w, true,
+        const Emitter em{cbuf[cb], &cbuf_n[cb], A.cands, A.ncand, A.cap, dm, (uint32_t)w, true,
                          A.sample_offset};
         Pending pe[3];
         step_fold(fl, hi, hq, ti, tq, k, pe);
@@ -588,7 +628,7 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
     for (uint32_t todo = (uint32_t)readfirst((int)carry_open) & ~smask & (0x1111u << wave); todo; todo &= todo - 1u) {
       const int j = __builtin_ctz(todo);
       const int w = 1 << j, sh = group_shift(w);
-      const Emitter em{cbuf[buf], &cbuf_n[buf], A.cands, A.ncand, A.cap, dm, (uint32_t)w, lane == 0,
+      const Emitter em{cbuf[cb], &cbuf_n[cb], A.cands, A.ncand, A.cap, dm, (uint32_t)w, lane == 0,
                        A.sample_offset};
       RunSum cj = carry[j];
       // nothing above for width j: a non-empty step closes an open run
@@ -612,23 +652,22 @@ __device__ __forceinline__ void detect_body(const DetectArgs& A, const int task)
   }
 
   __syncthreads();
-  const int lb = (nsteps - 1) & 1;  // staging buffer of the last step
   for (int j = wave; j < nw; j += 4) {
     const RunSum cj = carry[j];
-    const Emitter em{cbuf[lb], &cbuf_n[lb], A.cands, A.ncand, A.cap, dm, (uint32_t)(1 << j), lane == 0,
+    const Emitter em{cbuf[cb], &cbuf_n[cb], A.cands, A.ncand, A.cap, dm, (uint32_t)(1 << j), lane == 0,
                      A.sample_offset};
     if (A.nseg == 1 && !A.keep_edges) rs_close(cj, em);
     else if (lane == 0) A.frag[((int64_t)row * nw + j) * A.nseg + seg] = cj;
   }
   __syncthreads();
   if (tid == 0) {
-    const uint32_t n = min(cbuf_n[lb], (uint32_t)kCbuf);
+    const uint32_t n = min(cbuf_n[cb], (uint32_t)kCbuf);
     flush_n = n;
     flush_base = n ? atomicAdd(A.ncand, n) : 0u;
   }
   __syncthreads();
   for (uint32_t i = tid; i < flush_n; i += 256)
-    if (flush_base + i < A.cap) A.cands[flush_base + i] = cbuf[lb][i];
+    if (flush_base + i < A.cap) A.cands[flush_base + i] = cbuf[cb][i];
 }
 
 }  // namespace

@@ -21,15 +21,15 @@ namespace sps {
 namespace {
 
 constexpr int kFusedBins = 4096;
+constexpr int kFusedWords = 4 * (kFusedBins / 2);  // four chains' histograms, then the ring
 
 template <int NW, bool LEAD>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_search_batch(BatchStats S,
                                                                                              BatchDetect D) {
   __shared__ int s_task;
-  static_assert(4 * (kFusedBins / 2) <= kRing, "four chain histograms fit the ring");
   const int wave = readfirst((int)(threadIdx.x >> 6));
   const int lane = lane_id();
-  uint32_t* hist = detect_ring() + wave * (kFusedBins / 2);
+  uint32_t* hist = detect_ring<kFusedWords>() + wave * (kFusedBins / 2);
   // The chain loop has no lane-dependent branch: both atomics are issued by
   // the whole wave with an increment of 1 from lane 0 and 0 from the others.
   // A lane-0 branch at each end of the loop lets the compiler thread one into
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // every wave's own view, after the barrier
     int it = 0;
     while (it + 1 < D.nitems && D.offs[it + 1] <= task) ++it;
-    detect_body<NW, false>(D.items[it], task - D.offs[it]);
+    detect_body<NW, false, kFusedWords>(D.items[it], task - D.offs[it]);
     __syncthreads();
   }
 }

@@ -34,3 +34,19 @@ def test_validity_edges(n, top):
         print("detect edges", n, top, seg, flush=True)
         got, _, _ = gpu_search(x, top, L, 5.0, detect_seg=seg, capacity=4 * ref.size + 64)
         assert exact_equal(got, ref), (n, top, seg)
+
+
+@pytest.mark.parametrize("every", [2, 11, 40, 700, 5000])
+def test_staged_candidates(every):
+    # from several hundred candidates a step (past the staging buffers) to none for several steps
+    n, top, L = 30000, 16, 3000
+    x = 32768.0 + np.round(np.random.default_rng(every).normal(0.0, 1024.0, size=(3, n)))
+    x[0, ::every] += 30000.0
+    x[1, : n // 2 : every] += 30000.0
+    x[2, n - 1200 :: every] += 30000.0
+    x = x.astype(np.float32)
+    ref = oracle.search(x, top, L, 6.0)
+    for seg in (0, 1024, 8192):
+        print("staged candidates", every, seg, ref.size, flush=True)
+        got, _, _ = gpu_search(x, top, L, 6.0, detect_seg=seg, capacity=ref.size)
+        assert exact_equal(got, ref), (every, seg)
