@@ -56,6 +56,7 @@ struct StatsArgs {
   const int32_t* tmin; // device: no window reaches below *tmin (null: 0)
   int32_t* med;        // [rows][nblocks]
   int32_t* mad;
+  uint32_t* ncand;     // candidate counter that the launch clears for the detection after it (null: none)
   uint32_t* done;      // fused batch: per row, chains finished (null elsewhere)
 };
 

@@ -43,6 +43,7 @@ __global__ __launch_bounds__(64 * WPG) void k_block_stats(StatsArgs a) {
   // unit beside the vector work of the other waves
   const int wave = readfirst(threadIdx.x >> 6);
   const int chain = blockIdx.x * WPG + wave;
+  if (a.ncand && blockIdx.x == 0 && threadIdx.x == 0) *a.ncand = 0u;
   if (chain >= a.nchains) return;  // whole wave leaves; no block barriers are used
   stats_chain<NB, VIRT, LEAD>(a, chain, hist[wave], lane_id());
 }
