@@ -1503,7 +1503,13 @@ int sps_batch_search(sps_batch* b, const sps_batch_item* items, int32_t n, hipSt
     if (b->stats_seg == 0)
       shorten_first_segment(s.nblocks, std::min<int64_t>(it.baseline_len, it.nsamp), s.stats_nseg, s.stats_seg,
                             s.stats_head);
-    int64_t dseg = b->detect_seg > 0 ? b->detect_seg : std::max<int64_t>(std::min<int64_t>(total_samples / 8192, kLongSegment), 4LL * it.max_width);
+    // about 4096 detection tasks for the 1024 workgroups of the persistent
+    // launch: fewer halos than with 8192 (us, 8192 and 4096 tasks: 10 files of
+    // 256 x 131072, widths to 4096, 5015 and 4825; 6 of 300 x 40000, to 256, 1895
+    // and 1546; 24 of 64 x 65536, to 1024, 1943 and 1895; 3 of 64 x 30000 the same)
+    int64_t dseg = b->detect_seg > 0 ? b->detect_seg
+                                     : std::max<int64_t>(std::min<int64_t>(total_samples / 4096, kLongSegment),
+                                                         4LL * it.max_width);
     dseg = (dseg + kDetectStep - 1) / kDetectStep * kDetectStep;
     const int64_t nmax = std::max<int64_t>(kDetectStep, (it.nsamp + kDetectStep - 1) / kDetectStep * kDetectStep);
     dseg = std::max<int64_t>(kDetectStep, std::min<int64_t>(dseg, nmax));
