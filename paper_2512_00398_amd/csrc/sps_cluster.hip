@@ -309,6 +309,12 @@ __device__ __forceinline__ uint32_t snr_bits(const sps_cand& a) { return __float
 
 constexpr int kTilePos = 1024;     // positions per workgroup
 constexpr int kTileThreads = 512;
+// positions past a tile's end held in LDS: as many as leave three workgroups
+// per CU (51 KB each). Pairs further on are linked in global memory, which
+// dense time rows do much of (8.49 M candidates of 1024 trials, whole
+// clustering: 1024 held 3.45 ms, 2048 2.57; 2.1 M of 256 trials 0.55 for both;
+// 3072 at one workgroup per CU 2.80 and 0.60).
+constexpr int kCrossPos = 2048;
 // lanes that share one position's comparisons (the longest of a wave's loops is shorter)
 constexpr int kTileLanes = 4;
 
@@ -428,11 +434,13 @@ __global__ __launch_bounds__(kTileThreads) void k_cluster_tile(uint32_t n, int t
 // rows that reach the next tile's first row. Most of them join the same few
 // local components, so the components of the two tiles (by their roots'
 // positions) are joined in LDS first and each join is then made once in
-// global memory; pairs that reach past the next tile go there directly.
+// global memory; pairs that reach past the positions held go there directly.
 __global__ __launch_bounds__(kTileThreads) void k_cluster_cross(uint32_t n, int tt, int dt, int wt, ClusterScratch s) {
-  __shared__ __align__(16) sps_cand rec[2 * kTilePos];
-  __shared__ int root[2 * kTilePos];    // position's local root, from the tile's base
-  __shared__ int parent[2 * kTilePos];  // joined roots
+  constexpr int kHeld = kTilePos + kCrossPos;
+  static_assert(kHeld <= 65536, "positions from the tile's base fit 16 bits");
+  __shared__ __align__(16) sps_cand rec[kCrossPos];  // from the tile's end
+  __shared__ uint16_t root[kHeld];                   // position's local root, from the tile's base
+  __shared__ int parent[kHeld];                      // joined roots
   const uint32_t base = blockIdx.x * kTilePos, end = base + kTilePos;
   if (end >= n) return;
   const int tid = threadIdx.x;
@@ -446,23 +454,24 @@ __global__ __launch_bounds__(kTileThreads) void k_cluster_cross(uint32_t n, int 
   if (first >= end) return;               // whole workgroup; no barrier passed yet
   // the last position that any of them is compared with is in row cl + 1
   const uint32_t reach = cl + 2 <= nt ? s.count[(uint32_t)(cl + 2) * (uint32_t)nd] : n;
-  const uint32_t held = min(min(reach, n), end + kTilePos);
+  const uint32_t held = min(min(reach, n), end + kCrossPos);
   for (uint32_t p = first + tid; p < held; p += kTileThreads) {
     const int i = (int)(p - base);
-    rec[i] = s.sorted[p];
-    root[i] = s.members[p] ? i : s.slo[p] - (int)base;
+    if (p >= end) rec[p - end] = s.sorted[p];
+    root[i] = (uint16_t)(s.members[p] ? i : s.slo[p] - (int)base);
   }
-  for (int i = tid; i < 2 * kTilePos; i += kTileThreads) parent[i] = i;
+  const int len = (int)(held - base);
+  for (int i = tid; i < len; i += kTileThreads) parent[i] = i;
   __syncthreads();
   for (uint32_t p = first + tid / kTileLanes; p < end; p += kTileThreads / kTileLanes) {
-    const sps_cand a = rec[p - base];
+    const sps_cand a = s.sorted[p];
     const int la = log2w(a.width), ra = root[p - base];
     uint32_t e0, b1, e1;
     link_ranges(s, a, e0, b1, e1);
     auto link = [&](uint32_t b, uint32_t e) {
       for (uint32_t q = b + tid % kTileLanes; q < e; q += kTileLanes) {
         if (q < held) {
-          if (linked(a, la, rec[q - base], tt, dt, wt)) {
+          if (linked(a, la, rec[q - end], tt, dt, wt)) {
             const int rq = root[q - base];
             if (lds_ld(&parent[ra]) != lds_ld(&parent[rq])) lds_unite(parent, ra, rq);
           }
@@ -475,7 +484,7 @@ __global__ __launch_bounds__(kTileThreads) void k_cluster_cross(uint32_t n, int 
     link(max(b1, end), e1);
   }
   __syncthreads();
-  for (int i = tid; i < 2 * kTilePos; i += kTileThreads) {
+  for (int i = tid; i < len; i += kTileThreads) {
     const int r = lds_ld(&parent[i]);
     if (r != i) unite(s.parent, (int)base + r, (int)base + i);
   }
