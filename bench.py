@@ -41,14 +41,15 @@ KERNEL_SOURCES = {
                _CSRC + "sps_internal.h", _CSRC + "sps_api.hip", "include/sps.h"],
     "block_stats": [_CSRC + "sps_stats.hip", _CSRC + "sps_chain.h", _CSRC + "sps_wave.h", _CSRC + "sps_internal.h",
                     _CSRC + "sps_api.hip", "include/sps.h"],
-    "dedisp": [_CSRC + "sps_dedisp.hip", _CSRC + "sps_internal.h", _CSRC + "sps_api.hip", "include/sps.h"],
+    "dedisp": [_CSRC + "sps_dedisp.hip", _CSRC + "sps_dedisp_layout.h", _CSRC + "sps_internal.h",
+               _CSRC + "sps_api.hip", "include/sps.h"],
 }
 MEASURED_TRAFFIC = {
     # kernel: (sources hash, bytes per launch); profiles/kernels_c2_1024x2p20.md,
     # profiles/dedisp_1024ch_1024dm_2p18.md
-    "detect": ("28cb64f53eaf4840", (2237782 * 2 + 170188) * 1024),
-    "block_stats": ("83db0f9652526326", (4349769 * 2 + 137136) * 1024),
-    "dedisp": ("ba24418b892897af", (3431724 * 2 + 1048576) * 1024),
+    "detect": ("6ab946dc5891349c", (2323420 * 2 + 148378) * 1024),
+    "block_stats": ("4d73316708e25e29", (4348280 * 2 + 169519) * 1024),
+    "dedisp": ("b793660266c11b5d", (2834360 * 2 + 1048600) * 1024),
 }
 
 
@@ -57,8 +58,8 @@ MEASURED_TRAFFIC = {
 VALU_ISSUE_PER_S = 256 * 2.4e9
 MEASURED_VALU = {
     # kernel: (sources hash, SQ_INSTS_VALU per launch); profiles/kernels_c2_1024x2p20.md
-    "detect": ("28cb64f53eaf4840", 3.311e9),
-    "block_stats": ("83db0f9652526326", 1.875e9),
+    "detect": ("6ab946dc5891349c", 2.656e9),
+    "block_stats": ("4d73316708e25e29", 1.672e9),
 }
 
 
