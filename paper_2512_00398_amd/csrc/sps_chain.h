@@ -447,8 +447,8 @@ __device__ __forceinline__ void chain_step(Chain<NB, VIRT>& c, int lo, int hi, b
 // [kb_first, nblocks) of every row are computed; windows never reach below
 // the device value *tmin (the first sample of a stream). LEAD: the window
 // reaches a.lead samples past its block (false: trailing, offset compiled out).
-template <int NB, bool VIRT, bool LEAD>
-__device__ __forceinline__ void stats_chain(const StatsArgs& a, const int chain, uint32_t* H, const int lane) {
+template <int NB, bool VIRT, bool LEAD, class Args>
+__device__ __forceinline__ void stats_chain(const Args& a, const int chain, uint32_t* H, const int lane) {
   const int row = chain / a.nseg;
   const int seg = chain - row * a.nseg;
   // segment 0 has head_blocks blocks, the others seg_blocks each

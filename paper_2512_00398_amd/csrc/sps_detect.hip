@@ -46,21 +46,26 @@ __global__ __launch_bounds__(256) void k_detect(DetectArgs A) {
 // Persistent form over a batch of blocks: workgroups take (item, segment)
 // tasks from a queue (items ordered by segment length, longest first) until
 // none is left; every workgroup leaves once the counter passes the total.
-// Four waves per SIMD (at most 128 VGPRs): reading each item's arguments from
-// memory costs registers, and the kernel is faster at this occupancy even
-// with the two spilled registers it takes.
+// Five waves per SIMD (96 VGPRs, 3 of them spilled) as in k_detect: 105 without
+// the bound, 119 before the items' arguments were read by scalar loads, with
+// which five were slower than four (10 files of 256 x 131072, one launch per
+// stage: 5.02 ms, 4.83 with scalar loads, 4.54 with five waves).
 template <int NW, bool VIRT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_detect_batch(BatchDetect B) {
-  __shared__ int s_task;
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_detect_batch(BatchDetect B) {
+  // the task in the ring, which is free between tasks (a word of its own would
+  // cost the fifth workgroup per CU)
+  uint32_t* const ring = detect_ring<kRingWords>();
+  cst_i32* const offs = (cst_i32*)(uintptr_t)B.offs;
   while (true) {
-    if (threadIdx.x == 0) s_task = (int)atomicAdd(B.counter, 1u);
+    if (threadIdx.x == 0) ring[0] = atomicAdd(B.counter, 1u);
     __syncthreads();
-    const int task = __builtin_amdgcn_readfirstlane(s_task);
+    const int task = readfirst((int)ring[0]);
     __syncthreads();
     if (task >= B.total) break;
     int it = 0;
-    while (it + 1 < B.nitems && B.offs[it + 1] <= task) ++it;
-    detect_body<NW, VIRT>(B.items[it], task - B.offs[it]);
+    while (it + 1 < B.nitems && offs[it + 1] <= task) ++it;
+    it = readfirst(it);
+    detect_body<NW, VIRT>(((cst_DetectArgs*)(uintptr_t)B.items)[it], task - offs[it]);
     __syncthreads();
   }
 }

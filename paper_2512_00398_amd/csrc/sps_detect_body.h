@@ -235,8 +235,8 @@ __device__ __forceinline__ uint32_t* detect_ring() {
   return ring;
 }
 
-template <int NW, bool VIRT, int WORDS = kRingWords>
-__device__ __forceinline__ void detect_body(const DetectArgs& A, const int task) {
+template <int NW, bool VIRT, int WORDS = kRingWords, class Args>
+__device__ __forceinline__ void detect_body(const Args& A, const int task) {
   const int nw = NW > 0 ? NW : A.nw;
   uint32_t* const ring = detect_ring<WORDS>();
   __shared__ int32_t tlo[kMaxWidths][kGroups];

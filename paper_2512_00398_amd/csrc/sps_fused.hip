@@ -36,13 +36,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   // the other, which splits lane 0 from the rest of the wave across the back
   // edge; the other lanes then read the task from a lane that never took one.
   const uint32_t one = lane == 0 ? 1u : 0u;
+  cst_i32* const soffs = (cst_i32*)(uintptr_t)S.offs;
+  cst_i32* const doffs = (cst_i32*)(uintptr_t)D.offs;
   while (true) {
     const int task = readfirst((int)atomicAdd(S.counter, one));  // lane 0's value: the task taken
     if (task >= S.total) break;
     int it = 0;
-    while (it + 1 < S.nitems && S.offs[it + 1] <= task) ++it;
-    const StatsArgs& a = S.items[it];
-    const int chain = task - S.offs[it];
+    while (it + 1 < S.nitems && soffs[it + 1] <= task) ++it;
+    it = readfirst(it);
+    cst_StatsArgs& a = ((cst_StatsArgs*)(uintptr_t)S.items)[it];
+    const int chain = task - soffs[it];
     stats_chain<kFusedBins, false, LEAD>(a, chain, hist, lane);
     // every lane's stores of this chain, then the row's count
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
@@ -74,8 +77,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     if (task >= D.total) break;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // every wave's own view, after the barrier
     int it = 0;
-    while (it + 1 < D.nitems && D.offs[it + 1] <= task) ++it;
-    detect_body<NW, false, kFusedWords>(D.items[it], task - D.offs[it]);
+    while (it + 1 < D.nitems && doffs[it + 1] <= task) ++it;
+    it = readfirst(it);
+    detect_body<NW, false, kFusedWords>(((cst_DetectArgs*)(uintptr_t)D.items)[it], task - doffs[it]);
     __syncthreads();
   }
 }

@@ -54,16 +54,18 @@ __global__ __launch_bounds__(64 * WPG) void k_block_stats(StatsArgs a) {
 template <int NB, int WPG, bool VIRT, bool LEAD>
 __global__ __launch_bounds__(64 * WPG) void k_block_stats_batch(BatchStats B) {
   __shared__ __align__(16) uint32_t hist[WPG][NB / 2];
-  const int wave = threadIdx.x >> 6;
+  const int wave = readfirst(threadIdx.x >> 6);
   const int lane = lane_id();
   while (true) {
     uint32_t t = 0;
     if (lane == 0) t = atomicAdd(B.counter, 1u);
     const int task = __builtin_amdgcn_readfirstlane((int)t);
     if (task >= B.total) break;
+    cst_i32* const offs = (cst_i32*)(uintptr_t)B.offs;
     int it = 0;
-    while (it + 1 < B.nitems && B.offs[it + 1] <= task) ++it;
-    stats_chain<NB, VIRT, LEAD>(B.items[it], task - B.offs[it], hist[wave], lane);
+    while (it + 1 < B.nitems && offs[it + 1] <= task) ++it;
+    it = readfirst(it);
+    stats_chain<NB, VIRT, LEAD>(((cst_StatsArgs*)(uintptr_t)B.items)[it], task - offs[it], hist[wave], lane);
   }
 }
 
