@@ -47,8 +47,8 @@ KERNEL_SOURCES = {
 MEASURED_TRAFFIC = {
     # kernel: (sources hash, bytes per launch); profiles/kernels_c2_1024x2p20.md,
     # profiles/dedisp_1024ch_1024dm_2p18.md
-    "detect": ("6ab946dc5891349c", (2323420 * 2 + 148378) * 1024),
-    "block_stats": ("4d73316708e25e29", (4348280 * 2 + 169519) * 1024),
+    "detect": ("b0fae2b118e9947e", (2323470 * 2 + 148382) * 1024),
+    "block_stats": ("85938207f8012dbe", (4348280 * 2 + 169717) * 1024),
     "dedisp": ("b793660266c11b5d", (2834360 * 2 + 1048600) * 1024),
 }
 
@@ -58,8 +58,8 @@ MEASURED_TRAFFIC = {
 VALU_ISSUE_PER_S = 256 * 2.4e9
 MEASURED_VALU = {
     # kernel: (sources hash, SQ_INSTS_VALU per launch); profiles/kernels_c2_1024x2p20.md
-    "detect": ("6ab946dc5891349c", 2.656e9),
-    "block_stats": ("4d73316708e25e29", 1.672e9),
+    "detect": ("b0fae2b118e9947e", 2.656e9),
+    "block_stats": ("85938207f8012dbe", 1.672e9),
 }
 
 
