@@ -201,10 +201,51 @@ __device__ __forceinline__ uint32_t cell_of(const ClusterScratch& s, const sps_c
 }
 
 // Cell sizes, and each candidate's rank in its cell (in the order of the
-// atomics; kept in `parent` until the positions are known).
-__global__ void k_cluster_count(const sps_cand* c, uint32_t n, ClusterScratch s) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) s.parent[i] = (int)atomicAdd(&s.count[cell_of(s, c[i])], 1u);
+// atomics; kept in `parent` until the positions are known). Bound by the rate
+// of atomics on global memory (about 20 G/s): candidates that were written
+// together share cells, so a workgroup counts its 2048 in an LDS hash table
+// first and adds each cell's number once (2.1 M candidates 120 -> 78 us; 4096
+// in a table of 64 KB the same).
+constexpr int kCountThreads = 512;
+constexpr int kCountEach = 4;          // candidates per thread
+constexpr int kCountShift = 20;
+constexpr int kCountSlots = 1 << (32 - kCountShift);
+static_assert(kCountSlots >= 2 * kCountThreads * kCountEach, "an insertion always finds a free slot");
+
+__global__ __launch_bounds__(kCountThreads) void k_cluster_count(const sps_cand* c, uint32_t n, ClusterScratch s) {
+  __shared__ int key[kCountSlots];
+  __shared__ uint32_t cnt[kCountSlots];
+  for (int i = threadIdx.x; i < kCountSlots; i += kCountThreads) {
+    key[i] = -1;
+    cnt[i] = 0u;
+  }
+  __syncthreads();
+  const uint32_t base = blockIdx.x * (kCountThreads * kCountEach) + threadIdx.x;
+  int slot[kCountEach];
+  uint32_t rank[kCountEach];
+#pragma unroll
+  for (int k = 0; k < kCountEach; ++k) {
+    const uint32_t i = base + k * kCountThreads;
+    slot[k] = -1;
+    if (i < n) {
+      const int cell = (int)cell_of(s, c[i]);
+      int h = (int)(((uint32_t)cell * 2654435761u) >> kCountShift);
+      while (true) {  // at most half of the slots are ever taken
+        const int was = atomicCAS(&key[h], -1, cell);
+        if (was == -1 || was == cell) break;
+        h = (h + 1) & (kCountSlots - 1);
+      }
+      slot[k] = h;
+      rank[k] = atomicAdd(&cnt[h], 1u);
+    }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < kCountSlots; i += kCountThreads)
+    if (key[i] != -1) cnt[i] = atomicAdd(&s.count[key[i]], cnt[i]);
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kCountEach; ++k)
+    if (slot[k] >= 0) s.parent[base + k * kCountThreads] = (int)(cnt[slot[k]] + rank[k]);
 }
 
 // Exclusive prefix sums of the used part of count[0 .. kClusterCells + 2), in place, in three
@@ -568,7 +609,8 @@ hipError_t launch_cluster(const sps_cand* c, uint32_t n, int tt, int dt, int wt,
     hipLaunchKernelGGL(k_cluster_range, dim3(std::min(256u, (n + 1023) / 1024)), b, 0, st, c, n, s);
     hipLaunchKernelGGL(k_cluster_geometry, dim3(1), dim3(64), 0, st, tt, dt, s);
     hipLaunchKernelGGL(k_cluster_clear, gc, b, 0, st, s);
-    hipLaunchKernelGGL(k_cluster_count, gn, b, 0, st, c, n, s);
+    hipLaunchKernelGGL(k_cluster_count, dim3((n + kCountThreads * kCountEach - 1) / (kCountThreads * kCountEach)),
+                       dim3(kCountThreads), 0, st, c, n, s);
     hipLaunchKernelGGL(k_scan_tiles, dim3(kScanTiles), b, 0, st, s);
     hipLaunchKernelGGL(k_scan_totals, dim3(1), dim3(1024), 0, st, s);
     hipLaunchKernelGGL(k_scan_add, gc, b, 0, st, s);

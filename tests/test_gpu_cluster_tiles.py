@@ -43,3 +43,15 @@ def test_time_rows_longer_than_a_tile():
     c = _cands(s, d, 1 << rng.integers(0, 3, size=s.size), rng.uniform(6, 30, size=s.size).astype(np.float32))
     check(c[rng.permutation(c.size)], 10, 4, 1, "long-rows")
     check(c[rng.permutation(c.size)], 9, 2, 0, "long-rows-apart")
+
+
+@pytest.mark.parametrize("n", [1, 2047, 2048, 2049, 6145])
+def test_cell_counts(n):
+    # workgroups count 2048 candidates in a table of their own: every one in a
+    # cell of its own (the table as full as it gets), a few cells each, one cell
+    rng = np.random.default_rng(n)
+    snr = rng.permutation(n).astype(np.float32) + 6
+    one = np.full(n, 4)
+    check(_cands(rng.permutation(n) * 1000, np.full(n, 3), one, snr), 2, 0, 0, "own-cells")
+    check(_cands(rng.integers(0, 7, size=n) * 1000, rng.integers(0, 3, size=n) * 50, one, snr), 2, 1, 0, "few-cells")
+    check(_cands(np.full(n, 9), np.full(n, 3), one, snr), 2, 0, 0, "one-cell")
