@@ -392,18 +392,25 @@ __device__ __forceinline__ void read_windows(WidthShared& sm, const int j, const
     }
     c0 = (int64_t)w.mlo + ((int64_t)a << gm);  // c in [c0, c0 + cw)
     // #{|key - c| <= d} = bd + the keys from cen on up to c + d + those below
-    // it down to c - d: at most upper(d), at least lower(d), for any such c,
-    // from the nearest bin edges; d in [da, db] keeps both ends inside the window
+    // it down to c - d, less those on the far side of c that are further than
+    // d from it (c +- d need not reach cen when d < |c - cen|): at most
+    // upper(d), at least lower(d), for any such c, from the nearest bin edges.
+    // d in [da, db] keeps both ends inside the window, and the keys nearer to
+    // cen than it within d of c; with none of those (dlo = 0) any d may be asked.
     const int64_t u0 = c0 - cen, u1 = c0 + cw - 1 - cen;  // c - cen in [u0, u1]
     const int64_t umin = u0 < -u1 ? u0 : -u1, umax = u1 > -u0 ? u1 : -u0;
-    int64_t da = dlo - 1 - umin;
+    int64_t da = dlo > 0 ? dlo - 1 - umin : 0;
     da = da > 0 ? da : 0;
     const int64_t db = dlo - 1 + ((int64_t)nd << gs) - umax;
     // distances dlo .. x in the window: x - dlo + 1 values
-    auto up = [&](int64_t x) { return (int)((x - dlo + 1 + g - 1) >> gs); };
-    auto down = [&](int64_t x) { return (int)((x - dlo + 1) >> gs); };
-    auto upper = [&](int64_t d) { return bd + CU(up(u1 + d)) + CL(up(d - u0)); };
-    auto lower = [&](int64_t d) { return bd + CU(down(u0 + d)) + CL(down(d - u1)); };
+    auto up = [&](int64_t x) { return x < dlo ? 0 : (int)((x - dlo + 1 + g - 1) >> gs); };
+    auto down = [&](int64_t x) { return x < dlo ? 0 : (int)((x - dlo + 1) >> gs); };
+    auto upper = [&](int64_t d) {
+      return (int64_t)bd + CU(up(u1 + d)) - CU(down(u0 - d - 1)) + CL(up(d - u0)) - CL(down(-u1 - d - 1));
+    };
+    auto lower = [&](int64_t d) {
+      return (int64_t)bd + CU(down(u0 + d)) - CU(up(u1 - d - 1)) + CL(down(d - u1)) - CL(up(-u0 - d - 1));
+    };
     if (da <= db && lower(db) > rho && (da == 0 || upper(da) <= rho)) {
       auto first = [&](auto&& f) {  // smallest d in [da, db] with f(d) > rho
         int64_t x = da, y = db;
