@@ -24,8 +24,13 @@
 // first window, which gives c, and #{|S - c| <= d} at every bin edge of the
 // second, whose smallest d above the rank is the MAD. Bins wider than one
 // value (few samples, wide ranges) narrow the windows for another pass, with
-// bounds in place of values. A width whose windows miss (data unlike their
-// sample) is left to the general selection: its full range, then levels of
+// bounds in place of values. Where one value holds much of a series (a row
+// blanked, padded or constant), its keys would all be added to the same bins:
+// a sample of one value needs no histogram, and the exact pass counts the keys
+// at the estimate with ballots and equal neighbours together (sps_width_stats of
+// 256 x 131072, constant rows: 3.60 ms without, 1.55 with full histograms, now
+// 0.74; rows blanked for two thirds: 2.91, 2.18 and 2.00). A width whose
+// windows miss (data unlike their sample) is left to the general selection: its full range, then levels of
 // 11-bit digits of the key's distance from the current lower bound (one
 // 2048-bin LDS histogram per width): a level histograms the keys inside the
 // current range, one wave per width finds the bin holding the wanted rank,
@@ -60,6 +65,12 @@ __device__ __forceinline__ int bits_of(uint32_t r) { return r == 0u ? 0 : 32 - _
 
 constexpr int kWMid = 512, kWSide = 768;  // bins of the three windows (512 + 2 x 768 = kWBins)
 static_assert(kWMid + 2 * kWSide == kWBins, "the windows fill a width's histogram");
+// A width is dense when more than one in so many sampled keys is in the median's
+// bin, and that is no wider than so many bits (a wider one holds that many keys
+// of any series with a few far values): many of these keys have one value, and
+// would all be added to the same bins.
+constexpr uint32_t kDenseShare = 8;
+constexpr int kDenseShift = 6;
 
 // Windows of the exact pass, on keys: the median's, [mlo, mlo + lim[0]), and
 // that of the distances from the key cen, [dlo, dlo + lim[1]), keys below cen
@@ -68,7 +79,7 @@ struct __align__(16) WidthWindows {
   uint32_t mlo, cen, dlo;
   uint32_t lim[2];
   int32_t sh[2];
-  int32_t pad;
+  int32_t dense;  // much of the series is expected to equal cen
 };
 
 struct WidthShared {
@@ -85,8 +96,9 @@ struct WidthShared {
   int32_t cen[kMaxWidths];  // the median c_w
   WidthWindows win[kMaxWidths];
   uint32_t below[kMaxWidths][2];  // keys below the first window, distances below the second
-  // 1 while the width is sought by windows, 0 when its cen and res are final,
-  // -1 when it is left to the general selection
+  // 1 while the width is sought by windows (2: they are set, no histogram of
+  // the sample), 0 when its cen and res are final, -1 when it is left to the
+  // general selection
   int32_t live[kMaxWidths];
 };
 
@@ -180,6 +192,11 @@ __device__ __forceinline__ void stream_row(const WidthStatsArgs& A, const int ro
     }
   }
   __syncthreads();
+}
+
+// The thread's four keys are one (long runs of one value: a row blanked or padded).
+__device__ __forceinline__ bool all_equal(const uint32_t (&key)[4]) {
+  return (key[0] == key[1]) & (key[1] == key[2]) & (key[2] == key[3]);
 }
 
 // Adds the thread's keys in range to width j's histogram (equal neighbouring
@@ -300,7 +317,8 @@ __device__ __forceinline__ int window_shift(int64_t span, int bins) {
 // d (in [d - ed, d + ed]), or live -1 where they would leave the keys' range.
 // One lane.
 __device__ __forceinline__ void set_windows(WidthShared& sm, const int j, const int64_t m0, const int64_t mspan,
-                                            const int64_t cen, const int64_t d0, const int64_t dspan) {
+                                            const int64_t cen, const int64_t d0, const int64_t dspan,
+                                            const bool dense) {
   WidthWindows& w = sm.win[j];
   const int gm = window_shift(mspan, kWMid), gd = window_shift(dspan, kWSide);
   const int64_t dlo = d0 > 0 ? d0 : 0;
@@ -316,8 +334,28 @@ __device__ __forceinline__ void set_windows(WidthShared& sm, const int j, const 
   w.lim[1] = (uint32_t)lim1;
   w.sh[0] = gm;
   w.sh[1] = gd;
+  w.dense = dense;
   sm.below[j][0] = sm.below[j][1] = 0u;
   sm.live[j] = ok ? 1 : -1;
+}
+
+// The smallest of x .. y for which the monotone f holds (it does for y), by one
+// wave, 64 candidates at a time: the search waits for one read of LDS a round,
+// two or three rounds for a window's bins.
+template <class F>
+__device__ __forceinline__ int first_of(int x, int y, const int lane, F&& f) {
+  while (x < y) {
+    const int step = (int)(((uint32_t)(y - x) + 63u) >> 6);
+    const uint64_t mk = ballot(f((int)min((int64_t)x + (int64_t)lane * step, (int64_t)y)));
+    if (!mk) {
+      x += 63 * step + 1;  // at most y, for which it holds
+    } else {
+      const int k = ctz(mk);
+      y = min(x + k * step, y);
+      if (k) x += (k - 1) * step + 1;
+    }
+  }
+  return y;
 }
 
 // First windows of width j from the histogram of its samples (lo, sh), by one
@@ -342,24 +380,25 @@ __device__ __forceinline__ void aim_windows(WidthShared& sm, const int j, const 
       return (double)a + (q - (double)k) * (double)(b - a);
     };
     const uint32_t rank = (tot - 1u) >> 1;
-    int k = 0;
-    for (int st = kWBins / 2; st > 0; st >>= 1)
-      if (pre(k + st) <= rank) k += st;
+    const int k = first_of(0, kWBins - 1, lane, [&](int b) { return pre(b + 1) > rank; });
     const uint32_t cnt = pre(k + 1) - pre(k);  // at least 1
     const double c = bin * ((double)k + ((double)(rank - pre(k)) + 0.5) / (double)cnt);
     const double half = 0.5 * (double)tot;
     double dl = 0.0, dh = bin * (double)kWBins;
-    for (int it = 0; it < 40 && dh - dl > 0.25; ++it) {
-      const double d = 0.5 * (dl + dh);
-      if (F(c + d) - F(c - d) > half) dh = d;
-      else dl = d;
+    while (dh - dl > 0.25) {  // 64 distances at a time
+      const double step = (dh - dl) * (1.0 / 64.0), d = dl + step * (double)(lane + 1);
+      const uint64_t mk = ballot(F(c + d) - F(c - d) > half);
+      if (!mk) break;
+      dl += step * (double)ctz(mk);
+      dh = dl + step;
     }
     // how far the estimates may be off: the interpolation and three deviations
     // of the sampled rank (fewer where neighbouring positions share samples)
     const double err = 0.25 * bin + (whole ? bin : bin * sqrt((double)tot) / (2.0 * (double)cnt) * spread);
     const int64_t em = (int64_t)err + 32, ed = (int64_t)(2.0 * err) + 32;
     const int64_t ck = (int64_t)sm.lo[j] + (int64_t)c;
-    if (lane == 0) set_windows(sm, j, ck - em, 2 * em, ck, (int64_t)dh - ed, 2 * ed);
+    const bool dense = sh <= kDenseShift && cnt > tot / kDenseShare;
+    if (lane == 0) set_windows(sm, j, ck - em, 2 * em, ck, (int64_t)dh - ed, 2 * ed, dense);
   }
   clear_bins(h, lane);
 }
@@ -370,59 +409,54 @@ __device__ __forceinline__ void read_windows(WidthShared& sm, const int j, const
   uint32_t* h = sm.hist[j];
   const uint32_t tot = prefix_bins(h, lane);
   const uint32_t rho = (uint32_t)(n - 1) >> 1;
-  const WidthWindows w = sm.win[j];
-  const int gm = w.sh[0], gs = w.sh[1];
-  const uint32_t bm = sm.below[j][0], bd = sm.below[j][1];
-  const uint32_t p0 = h[kWMid], p1 = h[kWMid + kWSide];
+  WidthWindows w = sm.win[j];  // the same in every lane: scalar branches and loops
+  w.mlo = (uint32_t)readfirst((int)w.mlo);
+  w.cen = (uint32_t)readfirst((int)w.cen);
+  w.dlo = (uint32_t)readfirst((int)w.dlo);
+  w.lim[0] = (uint32_t)readfirst((int)w.lim[0]);
+  w.lim[1] = (uint32_t)readfirst((int)w.lim[1]);
+  const int gm = readfirst(w.sh[0]), gs = readfirst(w.sh[1]);
+  const uint32_t bm = (uint32_t)readfirst((int)sm.below[j][0]), bd = (uint32_t)readfirst((int)sm.below[j][1]);
+  const uint32_t p0 = (uint32_t)readfirst((int)h[kWMid]), p1 = (uint32_t)readfirst((int)h[kWMid + kWSide]);
   const int nm = (int)(w.lim[0] >> gm), nd = (int)(w.lim[1] >> gs);  // bins in use
   auto FM = [&](int k) { return bm + h[k]; };  // #{key < mlo + (k << gm)}, k <= nm
   // keys below cen (L) and from it on (U) at distances dlo .. dlo + (k << gs) - 1, k <= nd
-  auto CL = [&](int k) { return h[kWMid + k] - p0; };
-  auto CU = [&](int k) { return (k == kWSide ? tot : h[kWMid + kWSide + k]) - p1; };
+  auto CL = [&](int k) { return (int)(h[kWMid + k] - p0); };
+  auto CU = [&](int k) { return (int)((k == kWSide ? tot : h[kWMid + kWSide + k]) - p1); };
   int live = -1;
   int64_t c0 = 0, d1 = 0, d2 = 0;
-  const int64_t cw = (int64_t)1 << gm, g = (int64_t)1 << gs;
-  const int64_t cen = w.cen, dlo = w.dlo;
+  const int64_t cw = (int64_t)1 << gm;
   if (FM(0) <= rho && FM(nm) > rho) {
-    int a = 0, b = nm;  // FM(a) <= rho < FM(b)
-    while (b - a > 1) {
-      const int m = (a + b) >> 1;
-      if (FM(m) <= rho) a = m;
-      else b = m;
-    }
+    const int a = first_of(1, nm, lane, [&](int k) { return FM(k) > rho; }) - 1;
     c0 = (int64_t)w.mlo + ((int64_t)a << gm);  // c in [c0, c0 + cw)
     // #{|key - c| <= d} = bd + the keys from cen on up to c + d + those below
     // it down to c - d, less those on the far side of c that are further than
     // d from it (c +- d need not reach cen when d < |c - cen|): at most
-    // upper(d), at least lower(d), for any such c, from the nearest bin edges.
-    // d in [da, db] keeps both ends inside the window, and the keys nearer to
-    // cen than it within d of c; with none of those (dlo = 0) any d may be asked.
-    const int64_t u0 = c0 - cen, u1 = c0 + cw - 1 - cen;  // c - cen in [u0, u1]
-    const int64_t umin = u0 < -u1 ? u0 : -u1, umax = u1 > -u0 ? u1 : -u0;
-    int64_t da = dlo > 0 ? dlo - 1 - umin : 0;
-    da = da > 0 ? da : 0;
-    const int64_t db = dlo - 1 + ((int64_t)nd << gs) - umax;
-    // distances dlo .. x in the window: x - dlo + 1 values
-    auto up = [&](int64_t x) { return x < dlo ? 0 : (int)((x - dlo + 1 + g - 1) >> gs); };
-    auto down = [&](int64_t x) { return x < dlo ? 0 : (int)((x - dlo + 1) >> gs); };
-    auto upper = [&](int64_t d) {
-      return (int64_t)bd + CU(up(u1 + d)) - CU(down(u0 - d - 1)) + CL(up(d - u0)) - CL(down(-u1 - d - 1));
+    // upper, at least lower, for any such c, from the nearest bin edges. D = d -
+    // dlo in [da, db] keeps both ends inside the window, and the keys nearer to
+    // cen than it within d of c; with none of those (dlo = 0) any d may be
+    // asked, and only then are there keys on the far side. (Windows are shorter
+    // than 2^30, so all of this fits 32 bits.)
+    const int g = 1 << gs;
+    const bool far = w.dlo == 0u;
+    const int u0 = (int)(c0 - (int64_t)w.cen), u1 = u0 + (int)cw - 1;  // c - cen in [u0, u1]
+    const int umin = min(u0, -u1), umax = -umin;
+    const int da = far ? 0 : -1 - umin, db = (nd << gs) - 1 - umax;
+    // distances dlo .. dlo + x: x + 1 values
+    auto up = [&](int x) { return x < 0 ? 0 : (x + g) >> gs; };
+    auto down = [&](int x) { return x < 0 ? 0 : (x + 1) >> gs; };
+    auto upper = [&](int D) {
+      const int n = (int)bd + CU(up(u1 + D)) + CL(up(D - u0));
+      return far ? n - CU(down(u0 - D - 1)) - CL(down(-u1 - D - 1)) : n;
     };
-    auto lower = [&](int64_t d) {
-      return (int64_t)bd + CU(down(u0 + d)) - CU(up(u1 - d - 1)) + CL(down(d - u1)) - CL(up(-u0 - d - 1));
+    auto lower = [&](int D) {
+      const int n = (int)bd + CU(down(u0 + D)) + CL(down(D - u1));
+      return far ? n - CU(up(u1 - D - 1)) - CL(up(-u0 - D - 1)) : n;
     };
-    if (da <= db && lower(db) > rho && (da == 0 || upper(da) <= rho)) {
-      auto first = [&](auto&& f) {  // smallest d in [da, db] with f(d) > rho
-        int64_t x = da, y = db;
-        while (x < y) {
-          const int64_t m = (x + y) >> 1;
-          if (f(m) > rho) y = m;
-          else x = m + 1;
-        }
-        return x;
-      };
-      d1 = first(upper);
-      d2 = first(lower);
+    const bool first_d = (int64_t)w.dlo + da == 0;  // no smaller d to rule out
+    if (da <= db && lower(db) > (int)rho && (first_d || upper(da) <= (int)rho)) {
+      d1 = (int64_t)w.dlo + first_of(da, db, lane, [&](int D) { return upper(D) > (int)rho; });
+      d2 = (int64_t)w.dlo + first_of(da, db, lane, [&](int D) { return lower(D) > (int)rho; });
       live = d1 == d2 && cw == 1 ? 0 : 1;
     }
   }
@@ -434,7 +468,7 @@ __device__ __forceinline__ void read_windows(WidthShared& sm, const int j, const
     } else if (live == 1) {
       // counts are exact at bin edges only, so the next windows count their own
       // keys below; margins so that the answer is not the first d tested
-      set_windows(sm, j, c0, cw, c0 + cw / 2, d1 - cw - 2, d2 - d1 + 2 * cw + 6);
+      set_windows(sm, j, c0, cw, c0 + cw / 2, d1 - cw - 2, d2 - d1 + 2 * cw + 6, w.dense);
       if (sm.win[j].sh[0] >= gm && sm.win[j].sh[1] >= gs) sm.live[j] = -1;  // no progress
     }
   }
@@ -505,7 +539,12 @@ __global__ __launch_bounds__(kWT) void k_width_stats(WidthStatsArgs A) {
       const uint32_t lo = (uint32_t)sm.mn[j] ^ 0x80000000u, hi = (uint32_t)sm.mx[j] ^ 0x80000000u;
       sm.lo[j] = lo;
       sm.sh[j] = max(0, bits_of(hi - lo) - kWBits);
-      if (sm.mn[j] > sm.mx[j]) sm.live[j] = -1;  // no sampled position
+      if (sm.mn[j] > sm.mx[j]) {
+        sm.live[j] = -1;  // no sampled position
+      } else if (lo == hi) {
+        set_windows(sm, j, (int64_t)lo - 32, 64, lo, 0, 64, true);  // nothing to sort into bins
+        if (sm.live[j] == 1) sm.live[j] = 2;
+      }
     }
     __syncthreads();
     {
@@ -518,22 +557,28 @@ __global__ __launch_bounds__(kWT) void k_width_stats(WidthStatsArgs A) {
       }
       // wide boxcars change little over 16 positions: a quarter of the lanes, in a long row
       const bool sparse = N >= 131072 && (lane & 3) != 0;
-      auto count = [&](int j, uint32_t key) {
+      auto count = [&](int j, uint32_t key, uint32_t n) {
         const uint32_t b = (key - lo[j]) >> sh[j];
-        if (key != kNoKey && b < (uint32_t)kWBins && !(sparse && j >= 6)) atomicAdd(&sm.hist[j][b], 1u);
+        if (key != kNoKey && b < (uint32_t)kWBins && !(sparse && j >= 6)) atomicAdd(&sm.hist[j][b], n);
       };
       const uint32_t active = widths_with(1);
       if (whole)
         stream_row<NWU, 4>(A, row, sm, nw, active, [&](int j, const uint32_t (&key)[4], bool, const bool (&)[4]) {
+          if (all_equal(key)) {
+            count(j, key[0], 4u);
+          } else {
 #pragma unroll
-          for (int q = 0; q < 4; ++q) count(j, key[q]);
+            for (int q = 0; q < 4; ++q) count(j, key[q], 1u);
+          }
         });
       else
         stream_row<NWU, 1>(A, row, sm, nw, active,
-                           [&](int j, const uint32_t (&key)[1], bool, const bool (&)[1]) { count(j, key[0]); });
+                           [&](int j, const uint32_t (&key)[1], bool, const bool (&)[1]) { count(j, key[0], 1u); });
     }
     for (int j = wave; j < nw; j += kWaves)
       if (sm.live[j] == 1) aim_windows(sm, j, lane, whole, j < 6 ? 3.0 : 3.0 * fmax(sqrt(32.0 / (double)(1 << j)), 0.3));
+    __syncthreads();
+    if (tid < nw && sm.live[tid] == 2) sm.live[tid] = 1;
     __syncthreads();
     for (int pass = 0; pass < 4; ++pass) {
       const uint32_t active = widths_with(1);
@@ -541,35 +586,73 @@ __global__ __launch_bounds__(kWT) void k_width_stats(WidthStatsArgs A) {
       uint32_t below[kMaxWidths][2];
 #pragma unroll
       for (int j = 0; j < kMaxWidths; ++j) below[j][0] = below[j][1] = 0u;
-      stream_row<NWU, 4>(A, row, sm, nw, active, [&](int j, const uint32_t (&key)[4], bool, const bool (&)[4]) {
+      uint32_t dense = 0;
+      for (int j = 0; j < nw; ++j) dense |= sm.win[j].dense ? 1u << j : 0u;
+      dense = (uint32_t)readfirst((int)(dense & active));
+      auto count = [&](int j, const uint32_t (&key)[4], auto DENSE) {
         const WidthWindows w = sm.win[j];
         const uint32_t ndlo = 0u - w.dlo;
         uint32_t* h = sm.hist[j];
+        bool at_cen[4];
+        if (DENSE) {
+          // the keys that equal cen by ballots, one addition to each of their bins for the wave
+          int n = 0;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            at_cen[q] = key[q] == w.cen;
+            n += popc(ballot(at_cen[q]));
+          }
+          if (lane == 0 && n) {
+            if (w.cen - w.mlo < w.lim[0]) atomicAdd(&h[(w.cen - w.mlo) >> w.sh[0]], (uint32_t)n);
+            if (w.dlo == 0u) atomicAdd(&h[kWMid + kWSide], (uint32_t)n);
+          }
+        }
         // one branch for the four keys: most waves have none inside a wide boxcar's windows
         uint32_t t[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           t[q] = key[q] - w.mlo;
+          if (DENSE) t[q] = at_cen[q] ? kNoKey : t[q];
           below[j][0] += key[q] < w.mlo ? 1u : 0u;
         }
         if (min(min(t[0], t[1]), min(t[2], t[3])) < w.lim[0]) {
+          if (DENSE && all_equal(key)) {
+            atomicAdd(&h[t[0] >> w.sh[0]], 4u);
+          } else {
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (t[q] < w.lim[0]) atomicAdd(&h[t[q] >> w.sh[0]], 1u);
+            for (int q = 0; q < 4; ++q)
+              if (t[q] < w.lim[0]) atomicAdd(&h[t[q] >> w.sh[0]], 1u);
+          }
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           // |key - cen| - dlo, modulo 2^32: above ~dlo for the distances below dlo
           asm("v_sad_u32 %0, %1, %2, %3" : "=v"(t[q]) : "v"(key[q]), "v"(w.cen), "v"(ndlo));
           below[j][1] += t[q] > ~w.dlo ? 1u : 0u;
+          if (DENSE) t[q] = at_cen[q] ? kNoKey : t[q];
         }
         if (min(min(t[0], t[1]), min(t[2], t[3])) < w.lim[1]) {
+          if (DENSE && all_equal(key)) {
+            atomicAdd(&h[(key[0] < w.cen ? kWMid : kWMid + kWSide) + (t[0] >> w.sh[1])], 4u);
+          } else {
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (t[q] < w.lim[1])
-              atomicAdd(&h[(key[q] < w.cen ? kWMid : kWMid + kWSide) + (t[q] >> w.sh[1])], 1u);
+            for (int q = 0; q < 4; ++q)
+              if (t[q] < w.lim[1])
+                atomicAdd(&h[(key[q] < w.cen ? kWMid : kWMid + kWSide) + (t[q] >> w.sh[1])], 1u);
+          }
         }
-      });
+      };
+      // (a loop of its own for rows with dense widths: their branch in every
+      // row's loop cost 4 %)
+      if (dense)
+        stream_row<NWU, 4>(A, row, sm, nw, active, [&](int j, const uint32_t (&key)[4], bool, const bool (&)[4]) {
+          if ((dense >> j) & 1u) count(j, key, std::true_type{});
+          else count(j, key, std::false_type{});
+        });
+      else
+        stream_row<NWU, 4>(A, row, sm, nw, active, [&](int j, const uint32_t (&key)[4], bool, const bool (&)[4]) {
+          count(j, key, std::false_type{});
+        });
 #pragma unroll
       for (int j = 0; j < kMaxWidths; ++j) {
         if (j >= nw || !((active >> j) & 1u)) continue;

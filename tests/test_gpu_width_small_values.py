@@ -62,3 +62,25 @@ def test_few_values(n, kind):
     else:                       # mostly zeros
         x = np.where(rng.random((rows, n)) < 0.3, rng.integers(1, 4, size=(rows, n)), 0)
     check(x.astype(np.float32), min(64, 1 << int(np.log2(n))), min(n, 900), kind)
+
+
+@pytest.mark.parametrize("kind", ["constant", "sampled-constant", "blanked", "padded", "two-runs", "rare"])
+@pytest.mark.parametrize("n", [100, 5001, 32767, 33000, 131072 + 70])
+def test_one_value_holds_much_of_the_series(n, kind):
+    rng = np.random.default_rng(n + len(kind))
+    x = np.full((6, n), 1000.0)
+    noise = np.round(rng.normal(0.0, 200.0, size=(6, n)))
+    if kind == "sampled-constant":  # every sampled position alike, the others not
+        x += np.where(np.arange(n) % 4 == 3, 0.0, noise)
+    elif kind == "blanked":         # rows blanked here and there, from nearly all to a tenth
+        for r in range(6):
+            x[r] += np.where(rng.random(n // 50 + 1).repeat(50)[:n] < 0.97 - 0.17 * r, 0.0, noise[r])
+    elif kind == "padded":          # noise, then nothing; the last row all of it
+        for r in range(6):
+            x[r, : n * r // 5] += noise[r, : n * r // 5]
+    elif kind == "two-runs":        # two values in long runs, from even to one in ten
+        for r in range(6):
+            x[r] += 3.0 * (rng.random(n // 100 + 1).repeat(100)[:n] < 0.5 - 0.08 * r)
+    elif kind == "rare":
+        x += np.where(rng.random((6, n)) < 0.02, 3.0, 0.0)
+    check(x.astype(np.float32), min(4096, 1 << int(np.log2(n))), min(n, 700), kind)
