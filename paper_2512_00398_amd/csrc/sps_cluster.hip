@@ -30,6 +30,7 @@
 #include <algorithm>
 #include <climits>
 
+#include "sps_cluster_cells.h"
 #include "sps_internal.h"
 #include "sps_wave.h"
 
@@ -163,36 +164,12 @@ __global__ void k_cluster_clear(ClusterScratch s) {
   if (i < used_cells(s)) s.count[i] = 0u;
 }
 
-// Cell sizes: at least dm_tol + 1 trials and time_tol + 1 samples, and large
-// enough that all cells fit in kClusterCells. geo: [0, 1] sample range, [2]
-// time cell width, [3] DM cells per time row, [4, 5] DM range, [6] DM cell
-// width, [7] time rows (rows x DM cells <= kClusterCells).
 __global__ void k_cluster_geometry(int time_tol, int dm_tol, ClusterScratch s) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
-  const int64_t tlo = s.geo[0], thi = s.geo[1], dlo = s.geo[4], dhi = s.geo[5];
-  const int64_t trange = thi >= tlo ? thi - tlo + 1 : 1, drange = dhi >= dlo ? dhi - dlo + 1 : 1;
-  // at most a quarter of the cells across DM, so that at least four time rows
-  // fit (a time cell width capped at INT_MAX still covers the int32 range)
-  int64_t cd = (int64_t)dm_tol + 1;
-  const int64_t dneed = (drange + kClusterCells / 4 - 1) / (kClusterCells / 4);
-  if (cd < dneed) cd = dneed;
-  const int64_t nd = (drange + cd - 1) / cd;
-  const int64_t nt_max = kClusterCells / nd;
-  int64_t cw = (int64_t)time_tol + 1;
-  const int64_t tneed = (trange + nt_max - 1) / nt_max;
-  if (cw < tneed) cw = tneed;
-  s.geo[2] = (int)(cw > INT_MAX ? INT_MAX : cw);
-  s.geo[3] = (int)nd;
-  s.geo[6] = (int)cd;
-  s.geo[7] = (int)((trange + cw - 1) / cw);
+  if (blockIdx.x == 0 && threadIdx.x == 0) cluster_cells(time_tol, dm_tol, s.geo);
 }
 
-// Cell of a candidate and its (time, DM) cell coordinates. The differences
-// from the range's start fit 32 unsigned bits.
 __device__ __forceinline__ uint32_t cell_of(const ClusterScratch& s, int sample, uint32_t dm, int& ct, int& cd) {
-  ct = (int)(((uint32_t)sample - (uint32_t)s.geo[0]) / (uint32_t)s.geo[2]);
-  cd = (int)((dm - (uint32_t)s.geo[4]) / (uint32_t)s.geo[6]);
-  return (uint32_t)ct * (uint32_t)s.geo[3] + (uint32_t)cd;
+  return cluster_cell(s.geo, sample, dm, ct, cd);
 }
 
 __device__ __forceinline__ uint32_t cell_of(const ClusterScratch& s, const sps_cand& a) {

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/sps.h"
+#include "sps_cluster_cells.h"
 
 namespace sps {
 
@@ -239,7 +240,6 @@ struct BatchDetect {
 };
 
 // Candidate clustering scratch (device arrays; n = candidates of a run).
-constexpr int kClusterCells = 1 << 22;  // time cells of the bucketing
 struct ClusterScratch {
   sps_cand* sorted;   // [cap] candidates in bucket order
   int32_t* parent;    // [cap] rank in the cell, then union-find over positions (parent <= position)
