@@ -149,13 +149,16 @@ __device__ __forceinline__ int hist_or_0(const uint32_t* H, int i) {
 // The cost is a few steps per 64 values moved, so a baseline that moves by a
 // large part of a sigma per block (a drift shorter than the window) stays
 // within a small factor of the narrow query. Returns false, with the chain
-// unchanged, when a pivot leaves the histogram.
+// unchanged, when a pivot leaves the histogram. It starts inside only if all
+// three pivots are: a new histogram is centred on other samples than the pivots
+// come from, and with samples outside the input domain the differences wrap
+// (each test below is of a value that cannot).
 template <int NB, bool VIRT>
 __device__ __forceinline__ bool walk_query(Chain<NB, VIRT>& c) {
   const int rho = (c.n - 1) >> 1, lane = c.lane;
-  const int im = c.m - c.base;
-  int iL = im - c.d, iU = im + c.d + 1;
-  if (c.d < 0 || iL < 0 || iU > NB) return false;
+  const int im = (int)((uint32_t)c.m - (uint32_t)c.base);
+  if ((uint32_t)im >= (uint32_t)NB || (uint32_t)c.d > (uint32_t)min(im, NB - 1 - im)) return false;
+  int iL = im - c.d, iU = im + c.d + 1;  // in [0, NB]
   // median: windows of 64 bins from p, cp = #{x < base + p}
   int p = im - 32;
   int h = hist_or_0<NB>(c.H, p + lane), inc = wave_scan_incl(h);
