@@ -50,24 +50,59 @@ struct Chain {
   bool raw;           // histogram not maintained (data too spread)
 };
 
+// f(x, ok) for samples lo + lane, lo + 64 + lane, ... of the window [lo, hi) (ok:
+// inside it; else x is its last sample). Bound by load latency: the next eight
+// wave loads are in flight while eight are used (one load at a time, a
+// 4096-sample recount took 64 dependent round trips to L2).
+template <bool VIRT, class F>
+__device__ __forceinline__ void each_sample(const RowRef<VIRT>& row, int lo, int hi, int lane, F&& f) {
+  constexpr int kU = 8;
+  float nv[kU];
+  auto fetch = [&](int t0) {
+#pragma unroll
+    for (int q = 0; q < kU; ++q) nv[q] = row.at(min(t0 + 64 * q + lane, hi - 1));
+  };
+  fetch(lo);
+  int t0 = lo;
+  for (; t0 + 64 * kU <= hi; t0 += 64 * kU) {
+    float v[kU];
+#pragma unroll
+    for (int q = 0; q < kU; ++q) v[q] = nv[q];
+    fetch(t0 + 64 * kU);
+#pragma unroll
+    for (int q = 0; q < kU; ++q) f((int)v[q], true);
+  }
+#pragma unroll
+  for (int q = 0; q < kU; ++q)
+    if (t0 + 64 * q < hi) f((int)nv[q], t0 + 64 * q + lane < hi);
+}
+
 // Element of 0-based rank `rank` of the keys of samples [lo, hi):
 // MODE 0 keys are x ^ 0x80000000 (order of int32 x), MODE 1 keys are |x - m|.
 // Four passes over the window, 8 key bits each; H[0..255] serves as the
 // digit histogram (callers recount or abandon the value histogram afterwards).
+// The upper digits are one value for most samples, whose additions to one word
+// would take their turns in LDS: the lanes that share the first lane's digit
+// make one (256 x 131072, window 4096, noise of sigma 20000: 31.0 ms with one
+// load and one addition at a time, 28.9 with eight loads in flight, now 12.9).
 template <int MODE, bool VIRT>
 __device__ __forceinline__ uint32_t radix_select(uint32_t* H, const RowRef<VIRT>& row, int lo, int hi, int rank, int m, int lane) {
   uint32_t prefix = 0, pmask = 0;
   for (int shift = 24; shift >= 0; shift -= 8) {
     for (int i = lane; i < 256; i += 64) H[i] = 0;
     wave_lds_fence();
-    for (int t0 = lo; t0 < hi; t0 += 64) {
-      const int t = t0 + lane;
-      if (t < hi) {
-        const int v = row.iat(t);
-        const uint32_t key = MODE == 0 ? ((uint32_t)v ^ 0x80000000u) : absdiff(v, m);
-        if ((key & pmask) == prefix) atomicAdd(&H[(key >> shift) & 255u], 1u);
+    each_sample(row, lo, hi, lane, [&](int v, bool ok) {
+      const uint32_t key = MODE == 0 ? ((uint32_t)v ^ 0x80000000u) : absdiff(v, m);
+      const bool in = ok && (key & pmask) == prefix;
+      const uint32_t digit = (key >> shift) & 255u;
+      const uint64_t any = ballot(in);
+      if (any) {
+        const int first = ctz(any);
+        const bool same = in && digit == (uint32_t)readlane((int)digit, first);
+        const int n = popc(ballot(same));
+        if (in && (!same || lane == first)) atomicAdd(&H[digit], same ? (uint32_t)n : 1u);
       }
-    }
+    });
     wave_lds_fence();
     const int c0 = (int)H[4 * lane], c1 = (int)H[4 * lane + 1], c2 = (int)H[4 * lane + 2];
     const int c3 = (int)H[4 * lane + 3];
@@ -94,12 +129,9 @@ __device__ __forceinline__ uint32_t radix_select(uint32_t* H, const RowRef<VIRT>
 
 // Recount the window [lo, hi) into a histogram centred on `centre`, and the
 // pivots' counts for median m0 and MAD d0 (guesses or known values) from the
-// samples themselves. Bound by load latency: the next eight wave loads are in
-// flight while eight are counted (one load at a time, a 4096-sample recount took 64 dependent
-// round trips to L2).
+// samples themselves.
 template <int NB, bool VIRT>
 __device__ __forceinline__ void recount(Chain<NB, VIRT>& c, int lo, int hi, int centre, int m0, int d0) {
-  constexpr int kU = 8;
   c.base = centre - NB / 2;
   c.m = m0;
   c.d = d0;
@@ -107,29 +139,14 @@ __device__ __forceinline__ void recount(Chain<NB, VIRT>& c, int lo, int hi, int 
   wave_lds_fence();
   const int pL = m0 - d0, pU = m0 + d0 + 1;
   int cm = 0, cL = 0, cU = 0;
-  float nv[kU];
-  auto fetch = [&](int t0) {
-#pragma unroll
-    for (int q = 0; q < kU; ++q) nv[q] = c.row.at(min(t0 + 64 * q + c.lane, hi - 1));
-  };
-  fetch(lo);
-  for (int t0 = lo; t0 < hi; t0 += 64 * kU) {
-    float v[kU];
-#pragma unroll
-    for (int q = 0; q < kU; ++q) v[q] = nv[q];
-    fetch(t0 + 64 * kU);
-#pragma unroll
-    for (int q = 0; q < kU; ++q) {
-      const bool ok = t0 + 64 * q + c.lane < hi;
-      const uint64_t okm = ballot(ok);
-      const int x = (int)v[q];
-      const uint32_t idx = (uint32_t)x - (uint32_t)c.base;
-      if (ok && idx < (uint32_t)NB) hist_add(c.H, idx, 1u);
-      cm += popc(ballot(x < m0) & okm);
-      cL += popc(ballot(x < pL) & okm);
-      cU += popc(ballot(x < pU) & okm);
-    }
-  }
+  each_sample(c.row, lo, hi, c.lane, [&](int x, bool ok) {
+    const uint64_t okm = ballot(ok);
+    const uint32_t idx = (uint32_t)x - (uint32_t)c.base;
+    if (ok && idx < (uint32_t)NB) hist_add(c.H, idx, 1u);
+    cm += popc(ballot(x < m0) & okm);
+    cL += popc(ballot(x < pL) & okm);
+    cU += popc(ballot(x < pU) & okm);
+  });
   wave_lds_fence();
   c.cm = cm;
   c.cL = cL;
