@@ -9,6 +9,7 @@
 
 #include "sps_dedisp_layout.h"
 #include "sps_internal.h"
+#include "sps_segments.h"
 
 struct sps_plan {
   int32_t ndm;
@@ -22,7 +23,8 @@ struct sps_plan {
   int64_t max_cands;
   // tuning (never changes results)
   int32_t stats_seg;   // blocks per baseline chain, 0 = auto
-  int32_t detect_seg;  // samples per detection segment, 0 = auto
+  int32_t detect_seg;  // samples per detection segment, 0 = auto_seg
+  int32_t auto_seg;    // detect_segment() of the plan's rows
   int32_t hist_bins;   // 4096 or 16384
   int32_t window;      // SPS_ATTR_WINDOW: 0 trailing, 1 centred (changes results)
   int32_t norm;        // SPS_ATTR_NORM: 0 per-block MAD, 1 one MAD per row, 2 one MAD per (row, width)
@@ -64,12 +66,8 @@ int ok() {
   return SPS_OK;
 }
 
-constexpr int kDetectStep = 1024;
-// Longer detection segments only where a CU has no more than four: with many
-// rounds, short ones even out better (1024 x 2^20, widths to 4096, fast and slow
-// drift: 65536 positions 6.52 and 2.98 ms, 131072 6.42 and 3.25, 262144 6.69
-// and 3.31, whole rows 7.85 and 3.30).
-constexpr int64_t kLongSegment = 65536;
+using sps::kDetectStep;
+using sps::kLongSegment;
 
 // Waves of the statistics kernel that the chip holds with 32 KB of histograms
 // per workgroup of four (256 CUs x 4 workgroups).
@@ -158,45 +156,16 @@ void stats_segments_clipped(const sps_plan* p, int64_t nb, int32_t& seg, int32_t
 
 // Positions per detection segment for rows of `npos` positions (tuning only).
 int detect_seg_for(const sps_plan* p, int64_t npos) {
-  int64_t seg = p->detect_seg;
-  const bool chosen = seg > 0;
-  if (!chosen) {
-    // about 8192 workgroups, more of a large block; each segment >= 4 x max_width
-    // so the halo stays small
-    const int64_t total = (int64_t)p->ndm * npos;
-    seg = std::min<int64_t>(total / 8192, kLongSegment);
-    seg = std::max<int64_t>(seg, 4LL * p->max_width);
-  }
-  seg = ((seg + kDetectStep - 1) / kDetectStep) * kDetectStep;
-  if (seg < kDetectStep) seg = kDetectStep;
+  if (p->detect_seg <= 0) return (int)sps::detect_segment(p->ndm, npos, p->max_width);
+  // cap at the row: one step-aligned segment covers it
   const int64_t nmax = (npos + kDetectStep - 1) / kDetectStep * kDetectStep;
-  if (seg > nmax) seg = nmax;
-  if (seg < kDetectStep) seg = kDetectStep;
-  if (chosen) return (int)seg;
-  // From there on, the segment with the fewest rounds of steps: a segment
-  // takes its own steps and its halo's, four workgroups fill a CU, fewer run
-  // their steps somewhat faster, and many even out segments of unlike cost
-  // (us, detection, 4 x max_width and the choice: 256 x 131072, widths to 4096:
-  // 194 and 163; 256 x 65536, to 1024: 126 and 92; 333 x 100003, to 512: 192
-  // and 158).
-  int64_t best = seg;
-  double best_t = 0.0;
-  for (int64_t per_row = (npos + seg - 1) / seg; per_row >= 1; --per_row) {
-    const int64_t s = ((npos + per_row - 1) / per_row + kDetectStep - 1) / kDetectStep * kDetectStep;
-    const int64_t wgs = (int64_t)p->ndm * ((npos + s - 1) / s);
-    const double per_cu = (double)((wgs + 255) / 256);
-    if (s > kLongSegment && per_cu > 4.0 && best_t > 0.0) continue;
-    const double steps = (double)(s / kDetectStep + (p->max_width + 64 + kDetectStep - 1) / kDetectStep);
-    const double t = steps * (per_cu <= 4.0 ? 0.4 + 0.15 * per_cu : std::ceil(per_cu / 4.0)) * (1.0 + 0.4 / per_cu);
-    if (best_t == 0.0 || t < best_t) {
-      best_t = t;
-      best = s;
-    }
-  }
-  return (int)best;
+  const int64_t seg = ((int64_t)p->detect_seg + kDetectStep - 1) / kDetectStep * kDetectStep;
+  return (int)std::max<int64_t>(kDetectStep, std::min(seg, nmax));
 }
 
-int auto_detect_seg(const sps_plan* p) { return detect_seg_for(p, p->nsamp); }
+// The same for the plan's own rows (looked at by every search: the choice is
+// made once, with the plan).
+int auto_detect_seg(const sps_plan* p) { return p->detect_seg > 0 ? detect_seg_for(p, p->nsamp) : p->auto_seg; }
 
 bool is_pow2(int64_t v) { return v > 0 && (v & (v - 1)) == 0; }
 
@@ -256,6 +225,7 @@ void plan_params(sps_plan* p, int32_t ndm, int64_t nsamp, int32_t max_width, int
   }
   p->max_cands = 1LL << 24;
   p->hist_bins = 4096;
+  p->auto_seg = (int32_t)sps::detect_segment(ndm, nsamp, max_width);
 }
 
 // Marks the end of a call's device work on `s` (plans with an event only).
@@ -1503,10 +1473,13 @@ int sps_batch_search(sps_batch* b, const sps_batch_item* items, int32_t n, hipSt
     if (b->stats_seg == 0)
       shorten_first_segment(s.nblocks, std::min<int64_t>(it.baseline_len, it.nsamp), s.stats_nseg, s.stats_seg,
                             s.stats_head);
-    // about 4096 detection tasks for the 1024 workgroups of the persistent
-    // launch: fewer halos than with 8192 (us, 8192 and 4096 tasks: 10 files of
-    // 256 x 131072, widths to 4096, 5015 and 4825; 6 of 300 x 40000, to 256, 1895
-    // and 1546; 24 of 64 x 65536, to 1024, 1943 and 1895; 3 of 64 x 30000 the same)
+    // about 4096 detection tasks for the 1024 workgroups of the fused launch or
+    // the 1280 of the per-stage one: fewer halos than with 8192 (us, 8192 and
+    // 4096 tasks, fused and per stage, drifting blocks: 10 files of 256 x 131072,
+    // widths to 4096, 4523 and 4453, 4434 and 4302; 6 of 300 x 40000, to 256, 1856
+    // and 1736, 1954 and 1901; 24 of 64 x 65536, to 1024, 2483 and 2461, 2680 and
+    // 2683; 3 of 64 x 30000, to 256, 510 and 413, 353 and 328). 3072 to 5120 tasks
+    // are within 3 % of each other.
     int64_t dseg = b->detect_seg > 0 ? b->detect_seg
                                      : std::max<int64_t>(std::min<int64_t>(total_samples / 4096, kLongSegment),
                                                          4LL * it.max_width);
