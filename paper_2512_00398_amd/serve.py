@@ -296,6 +296,15 @@ class GpuExecutor:
         self.kept: Dict[int, list] = collections.defaultdict(list)
         self.intervals: List[Tuple[int, float, float]] = []  # (beam, device start, device end) per gulp
         self.ref = None
+        # pinned words that gulps' counts are copied to, in blocks; a word is
+        # free again once its count has been read. (A pinned tensor for every
+        # gulp took a third of its 150 us of submission, and gulps of 200 us hardly
+        # met on the device.)
+        self.words: List[object] = []
+        self._more_words()
+
+    def _more_words(self) -> None:
+        self.words.extend(self.torch.empty((64,), dtype=self.torch.int32, pin_memory=True).split(1))
 
     def footprint(self, s: BeamSpec) -> int:
         return sps.footprint(s.ndm, s.nsamp, s.max_width, s.baseline_len, True) + self.slots * (16 * self.cap + 4)
@@ -346,7 +355,9 @@ class GpuExecutor:
         """Count copies and completion events of gulps just enqueued on hs."""
         torch = self.torch
         for rec, x, c, n, off in zip(recs, xs, cands, ncands, offs):
-            host_n = torch.empty((1,), dtype=torch.int32, pin_memory=True)
+            if not self.words:
+                self._more_words()
+            host_n = self.words.pop()
             with torch.cuda.stream(hs):
                 host_n.copy_(n, non_blocking=True)
             copied = torch.cuda.Event()               # count readable on the host
@@ -412,6 +423,7 @@ class GpuExecutor:
                 rec.started = self._clock(began)
                 self.intervals.append((rec.beam, rec.started, rec.done))
                 rec.ncand = int(host_n.item()) & 0xFFFFFFFF
+                self.words.append(host_n)
                 if rec.ncand > self.cap:
                     raise sps.SpsError(sps.SPS_ERR_OVERFLOW, "gulp %d of beam %d" % (rec.k, rec.beam))
                 if self.keep:
