@@ -69,50 +69,13 @@ int ok() {
 using sps::kDetectStep;
 using sps::kLongSegment;
 
-// Waves of the statistics kernel that the chip holds with 32 KB of histograms
-// per workgroup of four (256 CUs x 4 workgroups).
-constexpr int64_t kChainSlots = 4096;
-
-// Blocks per baseline chain for `ndm` rows of `nb` blocks (tuning only): one
-// to four workgroups per CU, whichever is modelled fastest. More, shorter
-// chains hide each other's latency (a block takes about 1 us in a lone chain;
-// with four workgroups on a CU each runs at 1 / 1.54 of its speed, measured
-// on 256 x 131072) but each recounts its first window, about as long as
-// `window` / 128 blocks. More chains than slots only add recounts. Measured
-// (us, statistics alone; before: chains of at least four windows):
-// 64 x 16384, window 4096: 2437 -> 66; 16 x 500000, window 3000: 2185 -> 173;
-// 256 x 65536, window 4096: 332 -> 161; 2048 x 65536, window 16384: 2078 -> 1001.
-int64_t chain_blocks(int64_t ndm, int64_t nb, int64_t window) {
-  const double recount = 10.0 + (double)window / 128.0;
-  int64_t best = nb;
-  double best_t = 0.0;
-  for (int k = 1; k <= 4; ++k) {
-    const int64_t per_row = std::max<int64_t>(1, kChainSlots * k / (4 * ndm));
-    const int64_t seg = std::max<int64_t>(std::min<int64_t>(nb, 4), (nb + per_row - 1) / per_row);
-    const double t = (recount + (double)seg) * (1.0 + 0.18 * (k - 1));
-    if (k == 1 || t < best_t) {
-      best = seg;
-      best_t = t;
-    }
-  }
-  return std::max<int64_t>(1, best);
-}
-
-// The same for one of several blocks in a launch with `total_blocks` in all:
-// chains of about the launch's share of a resident wave, even within a row,
-// each longer than its window's recount.
-int64_t chain_blocks_shared(int64_t nb, int64_t window, int64_t total_blocks) {
-  const int64_t want = std::max<int64_t>((total_blocks + kChainSlots - 1) / kChainSlots, 16 + window / 128);
-  const int64_t per_row = (nb + want - 1) / want;
-  return std::max<int64_t>(1, (nb + per_row - 1) / std::max<int64_t>(per_row, 1));
-}
-
 // Blocks per baseline chain for `nb` blocks per row of a plan (tuning only);
-// total_blocks > 0: in a launch with others.
-int stats_seg_for(const sps_plan* p, int64_t nb, int64_t total_blocks = 0) {
+// total_blocks > 0: in a launch with others, of `bins` bins.
+int stats_seg_for(const sps_plan* p, int64_t nb, int64_t total_blocks = 0, int bins = 0) {
   if (p->stats_seg > 0) return (int)std::min<int64_t>(p->stats_seg, std::max<int64_t>(nb, 1));
   const int64_t window = std::min<int64_t>(p->baseline_len, nb * sps::kStride);
-  return (int)(total_blocks > 0 ? chain_blocks_shared(nb, window, total_blocks) : chain_blocks(p->ndm, nb, window));
+  return (int)(total_blocks > 0 ? sps::chain_blocks_shared(nb, window, total_blocks, bins)
+                                : sps::chain_blocks(p->ndm, nb, window, p->hist_bins));
 }
 
 int auto_stats_seg(const sps_plan* p) { return stats_seg_for(p, p->nblocks); }
@@ -951,7 +914,8 @@ namespace {
 
 // Statistics of one gulp of stream s reading history buffer c: only the
 // gulp's blocks, windows reaching back into the history.
-sps::StatsArgs stream_stats_args(const sps_stream* s, const float* d_gulp, int c, int64_t total_blocks = 0) {
+sps::StatsArgs stream_stats_args(const sps_stream* s, const float* d_gulp, int c, int64_t total_blocks = 0,
+                                 int bins = 0) {
   const sps_plan* p = s->plan;
   sps::StatsArgs a;
   a.x = d_gulp;
@@ -964,7 +928,7 @@ sps::StatsArgs stream_stats_args(const sps_stream* s, const float* d_gulp, int c
   a.lead = 0;  // streams use the trailing window only
   a.nblocks = s->nbv;
   a.kb_first = s->Hb;
-  a.seg_blocks = stats_seg_for(p, s->nbv - s->Hb, total_blocks);
+  a.seg_blocks = stats_seg_for(p, s->nbv - s->Hb, total_blocks, bins);
   // A gulp of at most 2048 blocks keeps to chains of 64 blocks: it takes a
   // few waves of a chip that the gulps of other beams run on at the same time
   // (9 rows x 64 blocks: 0.23 ms a gulp with its detection, 0.7 before).
@@ -1464,7 +1428,8 @@ int sps_batch_search(sps_batch* b, const sps_batch_item* items, int32_t n, hipSt
     if (b->stats_seg > 0) {
       seg = b->stats_seg;
     } else {
-      seg = chain_blocks_shared(s.nblocks, std::min<int64_t>(it.baseline_len, it.nsamp), total_blocks);
+      seg = sps::chain_blocks_shared(s.nblocks, std::min<int64_t>(it.baseline_len, it.nsamp), total_blocks,
+                                     b->hist_bins);
     }
     seg = std::max<int64_t>(1, std::min<int64_t>(seg, s.nblocks));
     s.stats_seg = (int32_t)seg;
@@ -1720,7 +1685,7 @@ int sps_batch_push(sps_batch* b, sps_stream* const* streams, const float* const*
   for (int32_t i = 0; i < n; ++i)
     total_blocks += (int64_t)streams[i]->plan->ndm * (streams[i]->nbv - streams[i]->Hb);
   for (int32_t i = 0; i < n; ++i) {
-    st[(size_t)i] = stream_stats_args(streams[i], d_gulps[i], streams[i]->cur, n > 1 ? total_blocks : 0);
+    st[(size_t)i] = stream_stats_args(streams[i], d_gulps[i], streams[i]->cur, n > 1 ? total_blocks : 0, b->hist_bins);
     dt[(size_t)i] = stream_detect_args(streams[i], d_gulps[i], d_cands[i], d_ncand[i], streams[i]->cur);
   }
   std::stable_sort(ord.begin(), ord.end(), [&](int32_t x, int32_t y) {

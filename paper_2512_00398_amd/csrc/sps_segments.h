@@ -10,6 +10,52 @@ namespace sps {
 constexpr int kCus = 256;
 constexpr int kDetectStep = 1024;
 
+// Chains (waves) of the statistics kernel in a workgroup, and workgroups that a
+// CU holds: by their histograms, 32 KB for four chains of 4096 bins, 64 KB for
+// two of 16384.
+inline int64_t chain_waves(int bins) { return bins == 16384 ? 2 : 4; }
+inline int64_t chain_groups(int bins) { return bins == 16384 ? 2 : 4; }
+
+// Blocks per baseline chain for `ndm` rows of `nb` blocks: one workgroup per CU
+// up to as many as it holds, whichever is modelled fastest. More, shorter
+// chains hide each other's latency (a block takes about 1 us in a lone chain;
+// with four workgroups of four on a CU each runs at 1 / 1.54 of its speed,
+// measured on 256 x 131072) but each recounts its first window, about as long as
+// `window` / 128 blocks. More chains than the chip holds only add recounts.
+// Measured (us, statistics alone; with chains of at least four windows, then
+// this): 64 x 16384, window 4096: 2437, 66; 16 x 500000, window 3000: 2185, 173;
+// 256 x 65536, window 4096: 332, 161; 2048 x 65536, window 16384: 2078, 1001.
+// 16384 bins, whole calls (with that, with chains for the 4096 slots of 4096
+// bins, with their own 1024): 1024 x 2^18, window 16384: 3847, 2855, 2599; 32 x
+// 2^20, window 30000: 1479, 506, 391; 2000 x 5000, window 1000: 1919, 422, 339;
+// 64 x 16384, window 4096: 522, 61, 61.
+inline int64_t chain_blocks(int64_t ndm, int64_t nb, int64_t window, int bins) {
+  const double recount = 10.0 + (double)window / 128.0;
+  const double slower = bins == 16384 ? 0.02 : 0.18;  // (four chains of 16384 bins are one wave per SIMD)
+  int64_t best = nb;
+  double best_t = 0.0;
+  for (int64_t k = 1; k <= chain_groups(bins); ++k) {
+    const int64_t per_row = std::max<int64_t>(1, kCus * chain_waves(bins) * k / ndm);
+    const int64_t seg = std::max<int64_t>(std::min<int64_t>(nb, 4), (nb + per_row - 1) / per_row);
+    const double t = (recount + (double)seg) * (1.0 + slower * (double)(k - 1));
+    if (k == 1 || t < best_t) {
+      best = seg;
+      best_t = t;
+    }
+  }
+  return std::max<int64_t>(1, best);
+}
+
+// The same for one of several blocks in a launch with `total_blocks` in all:
+// chains of about the launch's share of a resident wave, even within a row,
+// each longer than its window's recount.
+inline int64_t chain_blocks_shared(int64_t nb, int64_t window, int64_t total_blocks, int bins) {
+  const int64_t slots = kCus * chain_waves(bins) * chain_groups(bins);
+  const int64_t want = std::max<int64_t>((total_blocks + slots - 1) / slots, 16 + window / 128);
+  const int64_t per_row = (nb + want - 1) / want;
+  return std::max<int64_t>(1, (nb + per_row - 1) / std::max<int64_t>(per_row, 1));
+}
+
 // Shortest detection segments are at most this long: short ones even out rows of unlike cost.
 constexpr int64_t kLongSegment = 65536;
 
