@@ -66,16 +66,18 @@ constexpr int64_t kLongSegment = 65536;
 //   up to four workgroups per CU are one round, somewhat shorter with fewer;
 //   more take rounds that are partly filled, partly made up as some end early;
 //   many workgroups even out segments of unlike cost;
-//   a row's segments are stitched one after another, each a fifth of a step.
+//   a row's segments are stitched one after another, each a seventh of a step.
 // Five workgroups fit a CU, but share its issue slots: with a round of five the
 // model does 2 % better on average and up to 17 % worse on single shapes.
 // Fitted on 32 shapes of 1 x 2^20 to 5000 x 2048, widths to 1 .. 4096, with and
-// without drift and at low thresholds, 5 to 30 lengths each: 6.4 % above the
+// without drift and at low thresholds, 5 to 30 lengths each: 6.5 % above the
 // best of each on average, 11.3 % without the stitching and with whole rounds
 // (us, the whole search of a quiet and of a drifting block, that rule and this
-// one: 1 x 2^20, widths to 64, 313 and 494, 99 and 191; 40 x 2^20, to 32, 398
-// and 801, 365 and 707; 128 x 2^18, to 256, 305 and 788, 300 and 733; 256 x
-// 131072 and 333 x 100003 the same; 2048 x 65536 gulps, drifting, 1653 and 1679).
+// one: 1 x 2^20, widths to 64, 312 and 494, 101 and 191; 40 x 2^20, to 32, 398
+// and 802, 364 and 704; 128 x 2^18, to 256, 304 and 786, 299 and 731; 1100 x
+// 30000, to 128, 443 and 1024, 434 and 983; 256 x 131072, 333 x 100003, 64 x
+// 16384 and gulps of 2048 x 65536 the same; 40 x 2^20 at a threshold of 2.5, with
+// a candidate in every 15 samples, 856, 891).
 inline int64_t detect_segment(int64_t ndm, int64_t npos, int64_t max_width) {
   int64_t seg = std::max<int64_t>(std::min<int64_t>(ndm * npos / 8192, kLongSegment), 4 * max_width);
   const int64_t nmax = (npos + kDetectStep - 1) / kDetectStep * kDetectStep;
@@ -89,8 +91,8 @@ inline int64_t detect_segment(int64_t ndm, int64_t npos, int64_t max_width) {
     const double per_cu = (double)((ndm * nseg + kCus - 1) / kCus);
     const double steps = (double)(s / kDetectStep + (max_width + 64 + kDetectStep - 1) / kDetectStep);
     const double full = (double)((ndm * nseg + 4 * kCus - 1) / (4 * kCus));
-    const double rounds = per_cu <= 4.0 ? 0.5 + 0.125 * per_cu : 0.6 * full + 0.4 * (0.25 * per_cu + 0.2);
-    const double t = steps * rounds * (1.0 + 0.8 / per_cu) + (nseg > 1 ? 0.2 * (double)nseg : 0.0);
+    const double rounds = per_cu <= 4.0 ? 0.7 + 0.075 * per_cu : 0.6 * full + 0.4 * (0.25 * per_cu + 0.2);
+    const double t = steps * rounds * (1.0 + 0.9 / per_cu) + (nseg > 1 ? 0.15 * (double)nseg : 0.0);
     if (best_t == 0.0 || t < best_t) {
       best_t = t;
       best = s;
