@@ -70,17 +70,16 @@ __device__ __forceinline__ int root_of(int* parent, int x) {
 // compare-and-swap that fails if it is no root any more.
 template <int SCOPE>
 __device__ __forceinline__ void join(int* parent, int a, int b) {
-  while (true) {
-    a = root_of<SCOPE>(parent, a);
-    b = root_of<SCOPE>(parent, b);
-    if (a == b) return;
-    if (a < b) {
-      const int t = a;
-      a = b;
-      b = t;
-    }
-    int seen = a;
-    if (__hip_atomic_compare_exchange_strong(&parent[a], &seen, b, __ATOMIC_RELAXED, __ATOMIC_RELAXED, SCOPE)) return;
+  a = root_of<SCOPE>(parent, a);
+  b = root_of<SCOPE>(parent, b);
+  while (a != b) {
+    const int later = max(a, b);
+    const int earlier = min(a, b);
+    int seen = later;
+    if (__hip_atomic_compare_exchange_strong(&parent[later], &seen, earlier, __ATOMIC_RELAXED, __ATOMIC_RELAXED, SCOPE))
+      return;
+    a = root_of<SCOPE>(parent, seen);  // where it was put meanwhile
+    b = root_of<SCOPE>(parent, earlier);
   }
 }
 
