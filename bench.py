@@ -38,18 +38,18 @@ ALU_PAIR_ADD_PEAK_TOPS = 2 * ALU_INT32_PEAK_TOPS
 _CSRC = "paper_2512_00398_amd/csrc/"
 KERNEL_SOURCES = {
     "detect": [_CSRC + "sps_detect.hip", _CSRC + "sps_detect_body.h", _CSRC + "sps_runs.h", _CSRC + "sps_wave.h",
-               _CSRC + "sps_internal.h", _CSRC + "sps_api.hip", "include/sps.h"],
-    "block_stats": [_CSRC + "sps_stats.hip", _CSRC + "sps_chain.h", _CSRC + "sps_wave.h", _CSRC + "sps_internal.h",
-                    _CSRC + "sps_api.hip", "include/sps.h"],
+               _CSRC + "sps_segments.h", _CSRC + "sps_internal.h", _CSRC + "sps_api.hip", "include/sps.h"],
+    "block_stats": [_CSRC + "sps_stats.hip", _CSRC + "sps_chain.h", _CSRC + "sps_wave.h", _CSRC + "sps_segments.h",
+                    _CSRC + "sps_internal.h", _CSRC + "sps_api.hip", "include/sps.h"],
     "dedisp": [_CSRC + "sps_dedisp.hip", _CSRC + "sps_dedisp_layout.h", _CSRC + "sps_internal.h",
                _CSRC + "sps_api.hip", "include/sps.h"],
 }
 MEASURED_TRAFFIC = {
     # kernel: (sources hash, bytes per launch); profiles/kernels_c2_1024x2p20.md,
     # profiles/dedisp_1024ch_1024dm_2p18.md
-    "detect": ("b0fae2b118e9947e", (2323470 * 2 + 148382) * 1024),
-    "block_stats": ("85938207f8012dbe", (4348280 * 2 + 169717) * 1024),
-    "dedisp": ("b793660266c11b5d", (2834360 * 2 + 1048600) * 1024),
+    "detect": ("04b09c04c2645ea9", (2237971 * 2 + 145245) * 1024),
+    "block_stats": ("fca6412d632b855d", (4348356 * 2 + 169297) * 1024),
+    "dedisp": ("08ada2418bdbea8b", (2828477 * 2 + 1048612) * 1024),
 }
 
 
@@ -58,8 +58,8 @@ MEASURED_TRAFFIC = {
 VALU_ISSUE_PER_S = 256 * 2.4e9
 MEASURED_VALU = {
     # kernel: (sources hash, SQ_INSTS_VALU per launch); profiles/kernels_c2_1024x2p20.md
-    "detect": ("b0fae2b118e9947e", 2.656e9),
-    "block_stats": ("85938207f8012dbe", 1.672e9),
+    "detect": ("04b09c04c2645ea9", 2.587e9),
+    "block_stats": ("fca6412d632b855d", 1.667e9),
 }
 
 

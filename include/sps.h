@@ -222,8 +222,8 @@ int sps_plan_get(const sps_plan* plan, int attr, int64_t* value);
  * events on its stream around each kernel. sps_timing_read waits for the
  * recorded events, writes the summed milliseconds per stage since the last
  * read to ms_out[SPS_NSTAGES] and the number of searches to *nsearch, and
- * resets the sums. Stages: 0 baseline/normalisation kernel, 1 fused
- * filter/detect kernel, 2 fix-up and counter reset, 3 plain per-stage path
+ * resets the sums. Stages: 0 baseline/normalisation kernel (which also resets
+ * the counter), 1 fused filter/detect kernel, 2 fix-up, 3 plain per-stage path
  * (whole search). Host-synchronous.
  */
 #define SPS_NSTAGES 4
@@ -367,7 +367,7 @@ int sps_footprint(int32_t ndm, int64_t nsamp, int32_t max_width, int32_t baselin
  * and the cluster's sample and DM extents.
  *
  * sps_cluster_create: device scratch for up to max_cands candidates per run
- *   (about 40 bytes per candidate plus 48 MiB of time-cell tables). NULL on
+ *   (48 bytes per candidate plus 16 MiB of cell counts). NULL on
  *   error (SPS_ERR_INVALID_ARG for max_cands = 0, SPS_ERR_OOM, SPS_ERR_HIP).
  * sps_cluster_run: clusters the n candidates at d_cands (device, caller-owned,
  *   as written by sps_search; n <= max_cands, given by the host) on `stream`.

@@ -7,8 +7,8 @@
 // Design (gfx950, wave64). One add per (trial, channel, sample) is far too
 // much for the vector units, but most of these sums are shared: the delays of
 // 1 to 4 neighbouring channels, relative to the first of them, take few
-// distinct patterns over the 16 trials of a workgroup (1.6 for pairs, 2.7 for
-// threes on 1024 channels and trials). So a workgroup first builds, for a
+// distinct patterns over the 8, 16 or 32 trials of a workgroup (1.6 and 2.7 for
+// pairs and threes over 16 trials, on 1024 channels and trials). So a workgroup first builds, for a
 // subband of G channels, the 16-bit sums of each pattern once, in LDS, over
 // the span that the pattern's trials need, and each trial then adds one
 // 16-bit subband sample where it would have added G bytes. The host lays out

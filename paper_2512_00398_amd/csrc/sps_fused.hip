@@ -5,8 +5,8 @@
 // only for the chains of its own row.
 //
 // Every wave first takes statistics chains from the chain queue on its own,
-// its histogram in its quarter of the workgroup's detection ring (4 x 2048
-// words = the ring's 8192). A chain publishes its medians and MADs with an
+// its histogram in its quarter of the LDS that is the workgroup's detection ring
+// and staging later (4 x 2048 words, of which detection takes 6400). A chain publishes its medians and MADs with an
 // agent-scope release (the XCDs' L2 caches are not coherent for plain
 // stores) before it counts itself done for its row. When the chain queue is
 // empty the workgroup takes detection tasks; a task's first thread waits,
